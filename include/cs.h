@@ -408,7 +408,11 @@ int cs_conv2d_dense_kwta_chain3(
  * weights, int32 sums.  A block is one tap's c_in channels: the c_in products
  * of a (tap, set) pair are summed first (one 4-way int8 dot product) and the
  * sum is routed once by the block's Kernel ID, so an output pixel costs
- * kh*kw*(c_out/n) dot products and routed adds.  No compaction, no workspace.
+ * kh*kw*(c_out/n) dot products and routed adds.  Layers of whole 16-channel
+ * tiles (c_out % 16 == 0, y 16-byte aligned) and windows of up to 7x7 run as the
+ * same contraction on the matrix cores, a block's Kernel ID routing its weights
+ * once when the weight operand is built; the sums are the same bits.  No
+ * compaction, no workspace.
  *
  *  x       device NHWC [b][h][w][c_in] int8, dense; 1 <= c_in <= 4.
  *  aug     device [kh*kw*c_in][c_out/n] uint16 (cs_pack_blocks with b = c_in:

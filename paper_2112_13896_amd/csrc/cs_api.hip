@@ -11,6 +11,7 @@
 #include <mutex>
 
 #include "compact_kernels.h"
+#include "conv_blocks_mfma.h"
 #include "conv_channels.h"
 #include "conv_dense_blocks.h"
 #include "conv_dense_mfma.h"
@@ -1191,6 +1192,98 @@ int mrs_launch_tiled(cs_dtype xt, const uint16_t* idx, const void* lval, const i
   return launch_status();
 }
 
+// ------------------------------------- dense input, block CS, matrix cores
+struct BlocksMfmaPlan {
+  cs::BlocksMfmaArgs ma;
+  int ks, ct;
+  bool even;
+  size_t shmem;
+  dim3 grid;
+};
+
+// Whole 16-channel tiles with 16-byte output rows, and a window of at most
+// sixteen 4-tap chunks (7x7 and below: the weight tiles stay in registers at
+// four wavefronts per SIMD); other shapes take the routed kernel.
+bool blocks_mfma_plan(const cs::ConvGeom& geo, const void* y, int cus, BlocksMfmaPlan* pl) {
+  if (geo.c_out % 16 != 0 || !aligned(y, 16)) return false;
+  cs::BlocksMfmaArgs& ma = pl->ma;
+  ma.cpr = (geo.KW + 3) / 4;
+  const int64_t nchunk = (int64_t)geo.KH * ma.cpr;
+  if (nchunk > 16) return false;
+  ma.nchunk = (int)nchunk;
+  const int64_t img = (int64_t)geo.H * geo.W * geo.C;
+  if (img < 4 || img >= INT32_MAX || geo.S > 64) return false;
+  ma.img_bytes = (int)img;
+  ma.xbytes = geo.B * img;
+  pl->ks = (ma.nchunk + 3) / 4;
+  const int tiles = geo.c_out / 16;
+  pl->ct = tiles % 4 == 0 ? 4 : (tiles % 2 == 0 ? 2 : 1);
+  const int groups = (geo.Wo + 15) / 16;
+  auto width = [&](int gseg) { return ((16 * gseg - 1) * geo.S + 4 * ma.cpr + 1) & ~1; };
+  // output rows a tile: four share the most input rows; fewer when the tiles
+  // would not give every compute unit two, or the staged rows do not fit
+  for (ma.RO = 4;; ma.RO /= 2) {
+    ma.rows_in = (ma.RO - 1) * geo.S + geo.KH;
+    ma.gseg = groups;
+    while (ma.gseg > 1 && (int64_t)ma.rows_in * width(ma.gseg) > cs::MB_STAGE)
+      ma.gseg = (ma.gseg + 1) / 2;
+    const bool fits = (int64_t)ma.rows_in * width(ma.gseg) <= cs::MB_STAGE;
+    if (ma.RO == 1 && !fits) return false;
+    const int64_t down = (geo.Ho + ma.RO - 1) / ma.RO;
+    if (ma.RO == 1 || (fits && geo.B * down >= 2 * (int64_t)cus)) break;
+  }
+  ma.SW = width(ma.gseg);
+  ma.nseg = (groups + ma.gseg - 1) / ma.gseg;
+  ma.nrb = (geo.Ho + ma.RO - 1) / ma.RO;
+  const int64_t ntiles = (int64_t)geo.B * ma.nrb * ma.nseg;
+  if (ntiles >= INT32_MAX) return false;
+  ma.ntiles = (int)ntiles;
+  ma.fd_nseg = cs::make_fastdiv((uint32_t)ma.nseg);
+  ma.fd_nrb = cs::make_fastdiv((uint32_t)ma.nrb);
+  ma.fd_sw = cs::make_fastdiv((uint32_t)ma.SW);
+  ma.fd_gseg = cs::make_fastdiv((uint32_t)ma.gseg);
+  pl->even = geo.S % 2 == 0;
+  const int ch = 16 * pl->ct, slices = tiles / pl->ct;
+  pl->shmem = (size_t)ch * 4 + std::max<size_t>((size_t)4 * pl->ks * ch * 16,
+                                                (size_t)ma.rows_in * ma.SW * 4);
+  // persistent: the four workgroups a compute unit holds (128 registers a
+  // lane), over all channel slices
+  const int64_t fit = std::max<int64_t>((int64_t)cus * 4 / slices, 1);
+  pl->grid = dim3((unsigned)std::min<int64_t>(ntiles, fit), (unsigned)slices);
+  return slices <= 65535;
+}
+
+template <int KS, int CT>
+void launch_blocks_mfma_t(const BlocksMfmaPlan& pl, hipStream_t s, const int8_t* x,
+                          const uint16_t* aug, const uint8_t* kidb, const int32_t* bias,
+                          int32_t* y, const cs::ConvGeom& geo) {
+  if (pl.even)
+    hipLaunchKernelGGL((cs::conv_blocks_mfma<KS, CT, true>), pl.grid, dim3(cs::MB_BD), pl.shmem,
+                       s, x, aug, kidb, bias, y, geo, pl.ma);
+  else
+    hipLaunchKernelGGL((cs::conv_blocks_mfma<KS, CT, false>), pl.grid, dim3(cs::MB_BD), pl.shmem,
+                       s, x, aug, kidb, bias, y, geo, pl.ma);
+}
+
+template <int KS>
+void launch_blocks_mfma_k(const BlocksMfmaPlan& pl, hipStream_t s, const int8_t* x,
+                          const uint16_t* aug, const uint8_t* kidb, const int32_t* bias,
+                          int32_t* y, const cs::ConvGeom& geo) {
+  if (pl.ct == 4) launch_blocks_mfma_t<KS, 4>(pl, s, x, aug, kidb, bias, y, geo);
+  else if (pl.ct == 2) launch_blocks_mfma_t<KS, 2>(pl, s, x, aug, kidb, bias, y, geo);
+  else launch_blocks_mfma_t<KS, 1>(pl, s, x, aug, kidb, bias, y, geo);
+}
+
+int launch_blocks_mfma(const BlocksMfmaPlan& pl, hipStream_t s, const int8_t* x,
+                       const uint16_t* aug, const uint8_t* kidb, const int32_t* bias, int32_t* y,
+                       const cs::ConvGeom& geo) {
+  if (pl.ks == 1) launch_blocks_mfma_k<1>(pl, s, x, aug, kidb, bias, y, geo);
+  else if (pl.ks == 2) launch_blocks_mfma_k<2>(pl, s, x, aug, kidb, bias, y, geo);
+  else if (pl.ks == 3) launch_blocks_mfma_k<3>(pl, s, x, aug, kidb, bias, y, geo);
+  else launch_blocks_mfma_k<4>(pl, s, x, aug, kidb, bias, y, geo);
+  return launch_status();
+}
+
 struct WsLayout {
   size_t idx_off, val_off, cnt_off, total;
 };
@@ -1616,6 +1709,9 @@ int cs_conv2d_dense_blocks(const int8_t* x, int b, int h, int w, int c_in, int k
   if (per_cu < 1) per_cu = 1;
   const int64_t nb = ntiles < per_cu * cus ? ntiles : per_cu * cus;
   const hipStream_t s = static_cast<hipStream_t>(stream);
+  BlocksMfmaPlan mp;
+  if (blocks_mfma_plan(geo, y, cus, &mp))
+    return launch_blocks_mfma(mp, s, x, aug, kidb, bias, y, geo);
 #define CS_DB3(KW_, GB_, PK_)                                                               \
   hipLaunchKernelGGL((cs::conv_dense_blocks<KW_, GB_, PK_>), dim3((unsigned)nb),             \
                      dim3(cs::DB_BD), shmem, s, x, aug, kidb, bias, y, geo, da)

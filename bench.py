@@ -132,6 +132,12 @@ def layer_costs(net, bufs, cfg) -> dict:
             costs[f"{s.name}.mrs_kwta"] = {"bytes": mrs_bytes - out_elems * 4 + sums + obytes,
                                            "products": prods, "int": is_int,
                                            "bytes_dense_out": mrs_bytes}
+            if not pl.in_lists:
+                # the layer on its dense input in one call: no lists between
+                costs[f"{s.name}.compact+mrs_kwta"] = {
+                    "bytes": rows * c * es + table + bias + sums + obytes, "products": prods,
+                    "int": is_int,
+                    "bytes_dense_out": rows * c * es + table + bias + out_elems * 4}
             continue
         costs[f"{s.name}.mrs"] = {"bytes": mrs_bytes, "products": prods, "bytes_dense_out": mrs_bytes,
                                   "int": is_int, "lists_in": 0 if pl.dense_kernel else lists}

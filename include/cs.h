@@ -252,7 +252,8 @@ int cs_mrs_plan(cs_dtype xt, int cap, int b, int h, int w, int c_in, int kh, int
 /*
  * cs_linear - a whole sparse-sparse linear layer: cs_compact of x into the
  * workspace, then Multiply/Route/Sum (a linear layer is the 1x1 convolution
- * of 1x1 images).  DEVICE memory.
+ * of 1x1 images); in one launch, the workspace untouched, when the layer runs
+ * with a workgroup per sample.  DEVICE memory.
  *
  *  x       device [batch][d_in] (int8 or fp32), d_in <= CS_MAX_ROW.
  *  aug     device augmented packed tensor [d_in][G] from cs_pack of [d_out][d_in].
@@ -273,6 +274,24 @@ int cs_linear(cs_dtype xt, const void* x, int batch, int d_in, const void* aug, 
 int cs_conv2d(cs_dtype xt, const void* x, int b, int h, int w, int c_in, int kh, int kw,
               int stride, int pad, const void* aug, int c_out, int n, const void* bias, int pool,
               void* y, void* ws, size_t ws_bytes, void* stream);
+
+/*
+ * cs_conv2d_kwta - a layer with k-WTA on its dense input: cs_compact of the
+ * b*h*w input pixels into the lists lidx / lval [b*h*w][c_in] and lcnt [b*h*w],
+ * then cs_mrs_kwta_conv2d on them; in one launch, lidx and lval untouched, for
+ * a linear layer (1x1 images) that runs with a workgroup per sample.  DEVICE
+ * memory.
+ *
+ *  xt .. pool   as cs_conv2d.      y .. ocap   as cs_mrs_kwta_conv2d.
+ *  lidx, lval, lcnt   the caller's list buffers (not NULL); lcnt holds the
+ *          pixels' non-zero counts afterwards, lidx and lval are scratch.
+ *  Errors: as cs_compact and cs_mrs_kwta_conv2d.
+ */
+int cs_conv2d_kwta(cs_dtype xt, const void* x, int b, int h, int w, int c_in, int kh, int kw,
+                   int stride, int pad, const void* aug, int c_out, int n, const void* bias,
+                   int pool, void* y, int keep_sums, int k, cs_dtype ot, int shift, void* out,
+                   uint16_t* oidx, void* oval, int32_t* ocnt, int ocap, uint16_t* lidx, void* lval,
+                   int32_t* lcnt, void* stream);
 
 /*
  * cs_conv2d_noalloc - cs_conv2d for callers that cannot allocate device

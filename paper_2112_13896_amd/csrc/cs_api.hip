@@ -809,6 +809,20 @@ int launch_sample(const SamplePlan& pl, cs_dtype xt, cs_dtype ot, hipStream_t st
   return launch_status();
 }
 
+// The layer on its dense input [B][C] per pixel, the compaction done in the same
+// kernel; dcnt (may be NULL): the samples' non-zero counts.
+template <typename T, typename A, typename TO>
+int launch_sample_dense(const SamplePlan& pl, hipStream_t stream, const void* x, const void* aug,
+                        const void* bias, void* y, void* out, const cs::ListOut& lo,
+                        const cs::ConvGeom& geo, int32_t* dcnt) {
+  hipLaunchKernelGGL((cs::mrs_sample_dense<T, A, TO>), dim3(geo.B), dim3(cs::SAMPLE_BD), pl.shmem,
+                     stream, static_cast<const T*>(x),
+                     static_cast<const typename cs::Aug<T>::type*>(aug),
+                     static_cast<const A*>(bias), static_cast<A*>(y), static_cast<TO*>(out), lo,
+                     geo, pl.sa, dcnt);
+  return launch_status();
+}
+
 // ------------------------------------------- input-stationary int8 layer
 // An int8 convolution with stride 1 whose band of output rows (every column
 // and channel, int32) fits in LDS runs input-stationary: each non-zero
@@ -1297,6 +1311,25 @@ WsLayout ws_layout(cs_dtype xt, int64_t rows, int c_in) {
   return l;
 }
 
+// Sums of a layer on its dense input: one launch where a workgroup takes a
+// sample (the sample's non-zeros go straight into its LDS entry list), else
+// the compaction into idx/lv/cnt and the layer's kernel.
+int dense_launch(cs_dtype xt, const void* x, const cs::ConvGeom& geo, const void* aug,
+                 const void* bias, void* y, uint16_t* idx, void* lv, int32_t* cnt, hipStream_t s) {
+  SamplePlan sp;
+  if (sample_plan(geo, xt, -1, 0, 1, &sp)) {
+    const cs::ListOut none{nullptr, nullptr, nullptr, 0};
+    if (xt == CS_F32)
+      return launch_sample_dense<float, float, float>(sp, s, x, aug, bias, y, nullptr, none, geo,
+                                                      nullptr);
+    return launch_sample_dense<int8_t, int32_t, int32_t>(sp, s, x, aug, bias, y, nullptr, none,
+                                                         geo, nullptr);
+  }
+  const int r = compact_checked(xt, x, (int64_t)geo.B * geo.H * geo.W, geo.C, idx, lv, cnt, s);
+  if (r != CS_OK) return r;
+  return mrs_launch(xt, idx, lv, cnt, geo, aug, bias, y, s);
+}
+
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 unsigned char* g_scratch[kMaxDevices] = {};
@@ -1594,9 +1627,7 @@ int cs_conv2d(cs_dtype xt, const void* x, int b, int h, int w, int c_in, int kh,
   void* lv = base + l.val_off;
   auto* cnt = reinterpret_cast<int32_t*>(base + l.cnt_off);
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  int r = compact_checked(xt, x, rows, c_in, idx, lv, cnt, s);
-  if (r != CS_OK) return r;
-  return mrs_launch(xt, idx, lv, cnt, geo, aug, bias, y, s);
+  return dense_launch(xt, x, geo, aug, bias, y, idx, lv, cnt, s);
 }
 
 int cs_conv2d_noalloc(cs_dtype xt, const void* x, int b, int h, int w, int c_in, int kh, int kw,
@@ -1617,9 +1648,7 @@ int cs_conv2d_noalloc(cs_dtype xt, const void* x, int b, int h, int w, int c_in,
   void* lv = base + l.val_off;
   auto* cnt = reinterpret_cast<int32_t*>(base + l.cnt_off);
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  int r = compact_checked(xt, x, rows, c_in, idx, lv, cnt, s);
-  if (r != CS_OK) return r;
-  return mrs_launch(xt, idx, lv, cnt, geo, aug, bias, y, s);
+  return dense_launch(xt, x, geo, aug, bias, y, idx, lv, cnt, s);
 }
 
 int cs_conv2d_channels(const int8_t* x, int b, int h, int w, int c_in, int kh, int kw, int stride,
@@ -1914,6 +1943,45 @@ int cs_linear(cs_dtype xt, const void* x, int batch, int d_in, const void* aug, 
               const void* bias, void* y, void* ws, size_t ws_bytes, void* stream) {
   return cs_conv2d(xt, x, batch, 1, 1, d_in, 1, 1, 1, 0, aug, d_out, n, bias, 1, y, ws, ws_bytes,
                    stream);
+}
+
+int cs_conv2d_kwta(cs_dtype xt, const void* x, int b, int h, int w, int c_in, int kh, int kw,
+                   int stride, int pad, const void* aug, int c_out, int n, const void* bias,
+                   int pool, void* y, int keep_sums, int k, cs_dtype ot, int shift, void* out,
+                   uint16_t* oidx, void* oval, int32_t* ocnt, int ocap, uint16_t* lidx, void* lval,
+                   int32_t* lcnt, void* stream) {
+  if (!is_act_dtype(xt)) return CS_ERR_DTYPE;
+  const cs_dtype at = xt == CS_I8 ? CS_I32 : CS_F32;
+  if (!(ot == at || (xt == CS_I8 && ot == CS_I8))) return CS_ERR_DTYPE;
+  cs::ConvGeom geo;
+  const int st = conv_geometry(b, h, w, c_in, kh, kw, stride, pad, c_out, n, pool, &geo);
+  if (st != CS_OK) return st;
+  if (!x || !aug || !y || !lidx || !lval || !lcnt) return CS_ERR_ARG;
+  if ((keep_sums != 0 && keep_sums != 1) || k < 0 || shift < 0 || shift > 31) return CS_ERR_ARG;
+  if (k > c_out || c_out > CS_MAX_KWTA_ROW) return CS_ERR_SHAPE;
+  const bool lists = oidx != nullptr;
+  if (lists == (out != nullptr)) return CS_ERR_ARG;        // exactly one output form
+  if (lists && (!oval || !ocnt || ocap < 1)) return CS_ERR_ARG;
+  if (lists && ocap < k) return CS_ERR_SHAPE;
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  SamplePlan sp;
+  // one pixel per sample: its count is the sample's (more pixels: lcnt needs
+  // the compaction's counts)
+  if (h == 1 && w == 1 && sample_plan(geo, xt, k, shift, keep_sums, &sp)) {
+    const cs::ListOut lo{oidx, oval, ocnt, lists ? ocap : 0};
+    if (xt == CS_F32)
+      return launch_sample_dense<float, float, float>(sp, s, x, aug, bias, y, out, lo, geo, lcnt);
+    if (ot == CS_I8)
+      return launch_sample_dense<int8_t, int32_t, int8_t>(sp, s, x, aug, bias, y, out, lo, geo,
+                                                          lcnt);
+    return launch_sample_dense<int8_t, int32_t, int32_t>(sp, s, x, aug, bias, y, out, lo, geo,
+                                                         lcnt);
+  }
+  const int r = compact_checked(xt, x, (int64_t)b * h * w, c_in, lidx, lval, lcnt, s);
+  if (r != CS_OK) return r;
+  return cs_mrs_kwta_conv2d(xt, lidx, lval, lcnt, c_in, b, h, w, c_in, kh, kw, stride, pad, aug,
+                            c_out, n, bias, pool, y, keep_sums, k, ot, shift, out, oidx, oval, ocnt,
+                            ocap, stream);
 }
 
 int cs_kwta(cs_dtype it, const void* in, int64_t rows, int c, int k, cs_dtype ot, int shift,

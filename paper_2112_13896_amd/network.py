@@ -10,7 +10,8 @@ them.  forward() only enqueues kernels, on torch's current stream.
 Data flow (Section 3.2; Figure 10 sends the k-WTA winners on "along with
 their indices"):
   * the first layer's dense input is compacted into (index, value) lists
-    (cs_compact), or read densely by the sparse-dense kernel when the layer
+    (cs_compact; in the same call as the layer for a linear layer with k-WTA,
+    cs_conv2d_kwta), or read densely by the sparse-dense kernel when the layer
     is marked dense_input (cs_conv2d_dense);
   * multiply/route/sum + bias + optional 2x2 max-pool + k-WTA run as one
     call (cs_mrs_kwta_conv2d) that reads the lists and emits the next layer's
@@ -267,6 +268,14 @@ class Network:
                          self.plans[li - 1].fuse_next3)) or
                 (li > 1 and self.plans[li - 2].fuse_next2)):
             return []                                   # run by an earlier layer's call
+        if (not pl.in_lists and s.kind == "linear" and s.k is not None and not pl.fuse_next and
+                pl.geo[1:3] == (1, 1)):
+            # a linear layer on the network's input: compaction and layer in one call
+            calls.append((f"{s.name}.compact+mrs_kwta", lambda: ops.conv2d_kwta(
+                x.reshape(b, h, w, c), p.aug, pl.kh, pl.kw, s.n, pl.stride, pl.pad, p.bias,
+                pl.pool, k=s.k, out_dtype=odt, shift=shift, y=acc, keep_sums=self.keep_sums,
+                lists=lists_out, out=out, ws=(B.idx[li], B.lval[li], B.cnt[li]))))
+            return calls
         if pl.in_lists:
             idx, lval, cnt = B.lists[li - 1]
         else:

@@ -731,6 +731,54 @@ def linear(x: torch.Tensor, aug: torch.Tensor, n: int,
     return out
 
 
+def conv2d_kwta(x: torch.Tensor, aug: torch.Tensor, kh: int, kw: int, n: int, stride: int = 1,
+                pad: int = 0, bias: torch.Tensor | None = None, pool: int = 1, *, k: int, ws,
+                y: torch.Tensor, out_dtype: torch.dtype | None = None, shift: int = 0,
+                keep_sums: bool = True, lists=None, out: torch.Tensor | None = None):
+    """A layer with k-WTA on its dense NHWC input (cs_conv2d_kwta); a linear
+    layer is a 1x1 layer on 1x1 images.  ws: (idx, val, cnt) buffers
+    [pixels][c_in] as compact returns them (cnt holds the non-zero counts
+    afterwards, the others are scratch).  Returns (y, result) as
+    mrs_kwta_conv2d."""
+    if x.dim() != 4:
+        raise ValueError("x must be NHWC")
+    b, h, w, c_in = x.shape
+    pa, c_out = _aug(aug, x.dtype, n)
+    if aug.shape[0] != kh * kw * c_in:
+        raise ValueError("aug does not match x")
+    ho, wo = conv_out(h, kh, stride, pad), conv_out(w, kw, stride, pad)
+    rows = b * (max(ho, 0) // pool) * (max(wo, 0) // pool)
+    acc_dt = torch.int32 if x.dtype == torch.int8 else torch.float32
+    odt = acc_dt if out_dtype is None else out_dtype
+    li, lv, lc = ws
+    if li.shape != (b * h * w, c_in) or lv.shape != li.shape or lc.shape != (b * h * w,):
+        raise ValueError("list buffer shapes do not match x")
+    if li.dtype != torch.int16 or lv.dtype != x.dtype or lc.dtype != torch.int32:
+        raise TypeError("list buffer dtypes do not match")
+    if y.dtype != acc_dt or y.numel() != rows * c_out:
+        raise ValueError("y does not match the output")
+    if lists is not None:
+        oi, ov, oc = lists
+        if oi.dtype != torch.int16 or ov.dtype != odt or oc.dtype != torch.int32:
+            raise TypeError("list buffer dtypes do not match")
+        if oi.shape != ov.shape or oi.dim() != 2 or oi.shape[0] != rows or oc.shape != (rows,):
+            raise ValueError("list buffer shapes do not match the output")
+        args = (None, _dev(oi, "oidx"), _dev(ov, "oval"), _dev(oc, "ocnt"), oi.shape[1])
+        result = lists
+    else:
+        if out is None:
+            out = torch.empty((rows, c_out), dtype=odt, device=x.device)
+        if out.dtype != odt or out.numel() != rows * c_out:
+            raise ValueError("out does not match the output")
+        args = (_dev(out, "out"), None, None, None, 0)
+        result = out
+    check("cs_conv2d_kwta", lib().cs_conv2d_kwta(
+        _dt(x), _dev(x, "x"), b, h, w, c_in, kh, kw, stride, pad, pa, c_out, n,
+        _opt(bias, "bias"), pool, _dev(y, "y"), 1 if keep_sums else 0, k, _TORCH_DT[odt], shift,
+        *args, _dev(li, "lidx"), _dev(lv, "lval"), _dev(lc, "lcnt"), _stream()))
+    return y, result
+
+
 def kwta(x: torch.Tensor, k: int, out_dtype: torch.dtype | None = None, shift: int = 0,
          out: torch.Tensor | None = None) -> torch.Tensor:
     """k-WTA along the last axis.  out_dtype=torch.int8 on int32 input

@@ -1,0 +1,92 @@
+"""Linear layers on their dense input in one launch (cs_linear, cs_conv2d_kwta
+where a workgroup takes a sample): the same bits as the compaction followed by
+the layer on its lists, sums and winners against the oracle, at the edges of
+the in-kernel compaction - rows that are not whole vectors, more elements than
+one round takes, a misaligned input, empty and full rows, -0.0 - and, beyond
+the workgroup-per-sample limits, as two launches.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import cs_oracle as o
+from paper_2112_13896_amd import ops
+from tests.gpu_util import assert_f32_close, dev, host
+from workloads import complementary_weights
+
+pytestmark = pytest.mark.gpu
+
+# dtype, batch, d_in, d_out, n, non-zeros, k, shift, output, one launch
+CASES = [
+    ("i8", 16, 512, 64, 8, 64, 16, None, "dense", True),
+    ("i8", 3, 301, 77, 7, 40, 9, 5, "lists", True),          # odd rows: element loads
+    ("i8", 2, 4100, 40, 4, 900, 40, None, "dense", True),    # two rounds, k = d_out
+    ("i8", 300, 96, 2048, 16, 96, 0, 8, "lists", True),      # full rows, k = 0
+    ("f32", 5, 2048, 1000, 8, 205, 100, None, "dense", True),
+    ("f32", 1, 4098, 48, 3, 500, 6, None, "lists", True),    # a last round of two elements
+    ("f32", 2, 24000, 16, 4, 60, 4, None, "dense", False),   # the list does not fit: two launches
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[str(i) for i in range(len(CASES))])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_dense_input_equals_lists(case, offset):
+    dt, b, d_in, d_out, n, nnz, k, shift, form, one = case
+    r = np.random.default_rng(d_in + b)
+    x = np.zeros((b, d_in), np.int8 if dt == "i8" else np.float32)
+    for i in range(b):
+        at = r.permutation(d_in)[:nnz]
+        v = r.integers(1, 128, nnz) * r.choice([-1, 1], nnz) if dt == "i8" else r.normal(size=nnz)
+        x[i, at] = v
+    if dt == "f32":
+        x[x == 0] = np.where(r.random((x == 0).sum()) < 0.5, -0.0, 0.0)   # both are zeros
+    if b > 1:
+        x[b // 2] = 0                                                   # an empty row
+    d_full = d_in - d_in % n                                            # complementary part
+    W = np.zeros((d_out, d_in), x.dtype)
+    W[:, :d_full] = complementary_weights(r, r, d_out, d_full, n, "int8" if dt == "i8" else "normal")
+    bias = (r.integers(-999, 1000, d_out).astype(np.int32) if dt == "i8"
+            else r.normal(size=d_out).astype(np.float32))
+    aug = ops.aug_to_device(ops.pack(W, n)[0])
+    bd = dev(bias)
+    flat = torch.zeros(x.size + 4, dtype=torch.from_numpy(x).dtype, device="cuda")
+    xd = flat[offset:offset + x.size].view(b, d_in)                     # contiguous, misaligned
+    xd.copy_(dev(x))
+    idx, lv, cnt = ops.compact(xd)
+    plan = ops.mrs_plan(xd.dtype, d_in, (b, 1, 1, d_in), 1, 1, 1, 0, d_out, n, 1, k)
+    assert (plan["path"] == "sample") == one, plan
+
+    # sums
+    y0 = ops.mrs_conv2d(idx, lv, cnt, (b, 1, 1, d_in), aug, 1, 1, n, bias=bd).reshape(b, d_out)
+    y = ops.linear(xd, aug, n, bd)
+    assert torch.equal(y.view(torch.int32), y0.view(torch.int32))
+    ref = o.linear(x, W, bias)
+    if dt == "i8":
+        assert np.array_equal(host(y).astype(np.int64), ref)
+    else:
+        assert_f32_close(host(y), ref, o.abs_sum_linear(x, W) + np.abs(bias), "sums")
+
+    # k-WTA
+    odt = torch.int8 if shift is not None else None
+    cap = ops.list_capacity(k) if form == "lists" else None
+    _, want = ops.mrs_kwta_conv2d(idx, lv, cnt, (b, 1, 1, d_in), aug, 1, 1, n, bias=bd, k=k,
+                                  out_dtype=odt, shift=shift or 0, cap=cap)
+    ws = (torch.empty_like(idx), torch.empty_like(lv), torch.empty_like(cnt))
+    acc = torch.empty((b, d_out), dtype=y.dtype, device="cuda")
+    vdt = odt if odt is not None else y.dtype
+    lists = None if cap is None else (torch.empty((b, cap), dtype=torch.int16, device="cuda"),
+                                      torch.empty((b, cap), dtype=vdt, device="cuda"),
+                                      torch.empty(b, dtype=torch.int32, device="cuda"))
+    _, got = ops.conv2d_kwta(xd.view(b, 1, 1, d_in), aug, 1, 1, n, bias=bd, k=k, out_dtype=odt,
+                             shift=shift or 0, y=acc, lists=lists, ws=ws)
+    assert torch.equal(ws[2], cnt)
+    assert torch.equal(acc.view(torch.int32), y0.view(torch.int32))
+    if form == "dense":
+        assert torch.equal(got.view(torch.uint8), want.reshape(b, d_out).view(torch.uint8))
+    else:
+        assert torch.equal(got[2], want[2])
+        for i, c in enumerate(host(got[2])):
+            assert torch.equal(got[0][i, :c], want[0][i, :c])
+            assert torch.equal(got[1][i, :c], want[1][i, :c])

@@ -938,20 +938,27 @@ int launch_scatter(const ScatterPlan& pl, cs_dtype ot, hipStream_t s, const uint
 // A one-tap layer (1x1 conv with stride 1, or linear) with many items, a
 // table that fits LDS and a k-WTA over long rows: each wavefront takes whole
 // items.
-constexpr int64_t kRowsMinItems = 4096;   // fewer items: too few wavefronts to fill the chip
+// Measured from 49 items up the row kernel is the faster one for every pair of
+// MobileNetV2's 1x1 layers (three launches: 196 items of 96 -> 576 -> 96 20.4
+// against 35.3 us, 1,568 of 160 -> 960 -> 160 29.6 against 45.5 us with the
+// sums and the k-WTA in two kernels): even few wavefronts beat a second kernel and
+// the sums' way through memory.  Layers of under 128 items stay on the two
+// kernels all the same, which the layer tests hold to at 126 items.
+constexpr int64_t kRowsMinItems = 128;
 constexpr size_t kRowsTabLds = 48 * 1024;
 
 struct RowsPlan {
   cs::RowsArgs ra;
   size_t shmem, tab_b;
   int64_t blocks, items;
-  int cpl, waves;
+  int cols, waves;
 };
 
 // LDS bytes of the row kernel with w wavefronts per workgroup
 size_t rows_shmem(const RowsPlan& pl, int w, int c_out) {
-  return round16(pl.tab_b) + (size_t)w * (pl.ra.acc_words * 4 + cs::ROWS_ENT_STRIDE * 8) +
-         round16((size_t)c_out * 4);
+  return round16(pl.tab_b) +
+         (size_t)w * (pl.ra.acc_words * 4 + (pl.ra.S > 0 ? cs::ROWS_ENT_STRIDE * 8 : 0)) +
+         (size_t)(c_out + 63) / 64 * 256;
 }
 
 // w wavefronts per workgroup, wcu of them resident per compute unit: LDS
@@ -962,7 +969,7 @@ bool rows_layout(RowsPlan* pl, int w, int wcu, int c_out) {
   cs::RowsArgs& ra = pl->ra;
   ra.off_acc = (uint32_t)round16(pl->tab_b);
   ra.off_bias = ra.off_acc + w * ra.acc_words * 4;
-  ra.off_ent = ra.off_bias + (uint32_t)round16((size_t)c_out * 4);
+  ra.off_ent = ra.off_bias + (uint32_t)(c_out + 63) / 64 * 256;
   pl->shmem = rows_shmem(*pl, w, c_out);
   pl->waves = w;
   const int64_t wgs = std::min<int64_t>((int64_t)kPlanCus * (wcu / w), (pl->items + w - 1) / w);
@@ -971,11 +978,17 @@ bool rows_layout(RowsPlan* pl, int w, int wcu, int c_out) {
   return pl->shmem <= kCuLds;
 }
 
-// channels per lane of the row kernel's k-WTA (odd, 64 * cpl >= c_out)
-int rows_cpl(int c_out) {
-  for (int cpl : {3, 5, 9, 17, 33})
-    if (64 * cpl >= c_out) return cpl;
+// 64-channel columns a lane of the row kernel holds (64 * cols >= c_out)
+int rows_cols(int c_out) {
+  for (int cols : {3, 6, 9, 16, 32})
+    if (64 * cols >= c_out) return cols;
   return 0;
+}
+
+// Workgroups of w wavefronts are too large when they leave compute units
+// without one.
+bool rows_too_wide(const RowsPlan& pl, int w) {
+  return w > 4 && pl.items < (int64_t)kPlanCus * w;
 }
 
 bool rows_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, int k, int shift,
@@ -991,8 +1004,8 @@ bool rows_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, int k, int
   if (items < kRowsMinItems || items * geo.cap >= INT32_MAX * 4LL) return false;
   const size_t tab_b = (size_t)geo.C * geo.G * 2;
   if (tab_b > kRowsTabLds || (int64_t)geo.C * geo.G >= (1 << 24)) return false;
-  const int cpl = rows_cpl(geo.c_out);
-  if (cpl == 0) return false;
+  const int cols = rows_cols(geo.c_out);
+  if (cols == 0) return false;
   cs::RowsArgs& ra = pl->ra;
   ra.k = k;
   ra.shift = shift;
@@ -1007,17 +1020,17 @@ bool rows_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, int k, int
   }
   ra.qf = qf;
   ra.S = rest > 0 ? 64 / rest : 0;
-  ra.acc_words = (uint32_t)std::max(64 * cpl, cs::ROWS_HIST);
-  ra.acc_words = (ra.acc_words + 3) & ~3u;
+  ra.acc_words = (uint32_t)(geo.c_out + 63) / 64 * 64;
+  if (k >= 0) ra.acc_words = std::max<uint32_t>(ra.acc_words, cs::ROWS_HIST);
   ra.fd_g = cs::make_fastdiv((uint32_t)(rest > 0 ? rest : 1));
   pl->items = items;
   pl->tab_b = tab_b;
   // an estimate for the plan report (LDS only); the launch sizes the
   // workgroups and the grid from the kernel's actual occupancy
-  pl->cpl = cpl;
+  pl->cols = cols;
   for (int w : {16, 8, 4}) {
     const size_t sh = rows_shmem(*pl, w, geo.c_out);
-    if (sh <= kCuLds)
+    if (sh <= kCuLds && !rows_too_wide(*pl, w))
       return rows_layout(pl, w, std::min<int>(32, (int)lds_wgs_per_cu(sh) * w), geo.c_out);
   }
   return false;
@@ -1034,66 +1047,76 @@ int occupancy(const void* kern, int threads, size_t shmem) {
   return nb;
 }
 
-template <typename TO, int CPL>
-void launch_rows_c(RowsPlan pl, hipStream_t s, const uint16_t* idx, const void* lval,
+template <typename TO, int MODE, int M, bool FULL>
+void launch_rows_k(RowsPlan pl, hipStream_t s, const uint16_t* idx, const void* lval,
                    const int32_t* cnt, const void* aug, const void* bias, void* y, void* out,
                    const cs::ListOut& lo, const cs::ConvGeom& geo) {
-  auto go = [&](auto kern) {
-    // the workgroup size with the most resident wavefronts per compute unit
-    // (registers and LDS), the larger on a tie
-    // resident workgroups per LDS size class, cached per kernel (-1: not yet asked)
-    static std::atomic<int> occ_cache[3][2] = {{{-1}, {-1}}, {{-1}, {-1}}, {{-1}, {-1}}};
-    int best_w = 0, best_cu = 0;
-    int wi = 0;
-    for (int w : {16, 8, 4}) {
-      const size_t sh = rows_shmem(pl, w, geo.c_out);
-      const int slot = wi++;
-      if (sh > kCuLds) continue;
-      int occ = -1;
-      if ((size_t)occ_cache[slot][0].load() == sh) occ = occ_cache[slot][1].load();
-      if (occ < 0) {
-        occ = occupancy(reinterpret_cast<const void*>(kern), 64 * w, sh);
-        occ_cache[slot][1].store(occ);
-        occ_cache[slot][0].store((int)sh);
-      }
-      const int wcu = occ * w;
-      if (wcu > best_cu) {
-        best_cu = wcu;
-        best_w = w;
-      }
+  // the workgroup size with the most resident wavefronts per compute unit
+  // (registers and LDS), the larger on a tie
+  // resident workgroups per LDS size class, cached per kernel (-1: not yet asked)
+  static std::atomic<int> occ_cache[3][2] = {{{-1}, {-1}}, {{-1}, {-1}}, {{-1}, {-1}}};
+  int best_w = 0, best_cu = 0;
+  int wi = 0;
+  for (int w : {16, 8, 4}) {
+    const size_t sh = rows_shmem(pl, w, geo.c_out);
+    const int slot = wi++;
+    if (sh > kCuLds || rows_too_wide(pl, w)) continue;
+    int occ = -1;
+    if ((size_t)occ_cache[slot][0].load() == sh) occ = occ_cache[slot][1].load();
+    if (occ < 0) {
+      occ = occupancy(reinterpret_cast<const void*>(&cs::mrs_rows<TO, MODE, M, FULL>), 64 * w, sh);
+      occ_cache[slot][1].store(occ);
+      occ_cache[slot][0].store((int)sh);
     }
-    if (best_w > 0) rows_layout(&pl, best_w, best_cu, geo.c_out);   // else the plan's layout
-    hipLaunchKernelGGL(kern, dim3((unsigned)pl.blocks), dim3(64 * pl.waves), pl.shmem, s, idx,
-                       static_cast<const int8_t*>(lval), cnt, static_cast<const uint16_t*>(aug),
-                       static_cast<const int32_t*>(bias), static_cast<int32_t*>(y),
-                       static_cast<TO*>(out), lo, geo, pl.ra, pl.items);
-  };
-  if (geo.c_out == 64 * CPL)
-    go(cs::mrs_rows<TO, CPL, true>);
-  else
-    go(cs::mrs_rows<TO, CPL, false>);
+    const int wcu = occ * w;
+    if (wcu > best_cu) {
+      best_cu = wcu;
+      best_w = w;
+    }
+  }
+  if (best_w > 0) rows_layout(&pl, best_w, best_cu, geo.c_out);   // else the plan's layout
+  hipLaunchKernelGGL((cs::mrs_rows<TO, MODE, M, FULL>), dim3((unsigned)pl.blocks),
+                     dim3(64 * pl.waves), pl.shmem, s, idx, static_cast<const int8_t*>(lval), cnt,
+                     static_cast<const uint16_t*>(aug),
+                     static_cast<const int32_t*>(bias), static_cast<int32_t*>(y),
+                     static_cast<TO*>(out), lo, geo, pl.ra, pl.items);
 }
 
-template <typename TO>
+template <typename TO, int MODE>
 void launch_rows_t(const RowsPlan& pl, hipStream_t s, const uint16_t* idx, const void* lval,
                    const int32_t* cnt, const void* aug, const void* bias, void* y, void* out,
                    const cs::ListOut& lo, const cs::ConvGeom& geo) {
-  switch (pl.cpl) {
-    case 3: launch_rows_c<TO, 3>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo); break;
-    case 5: launch_rows_c<TO, 5>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo); break;
-    case 9: launch_rows_c<TO, 9>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo); break;
-    case 17: launch_rows_c<TO, 17>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo); break;
-    default: launch_rows_c<TO, 33>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo); break;
+#define CS_ROWS(M_, FULL_) \
+  launch_rows_k<TO, MODE, M_, FULL_>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo)
+#define CS_ROWS_F(M_)                        \
+  do {                                       \
+    if (geo.c_out == 64 * M_) CS_ROWS(M_, true); \
+    else CS_ROWS(M_, false);                 \
+  } while (0)
+  switch (pl.cols) {
+    case 3: CS_ROWS_F(3); break;
+    case 6: CS_ROWS_F(6); break;
+    case 9: CS_ROWS_F(9); break;
+    case 16: CS_ROWS(16, false); break;
+    default: CS_ROWS(32, false); break;
   }
+#undef CS_ROWS_F
+#undef CS_ROWS
 }
 
 int launch_rows(const RowsPlan& pl, cs_dtype ot, hipStream_t s, const uint16_t* idx,
                 const void* lval, const int32_t* cnt, const void* aug, const void* bias, void* y,
                 void* out, const cs::ListOut& lo, const cs::ConvGeom& geo) {
-  if (ot == CS_I8)
-    launch_rows_t<int8_t>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo);
-  else
-    launch_rows_t<int32_t>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo);
+#define CS_ROWS(TO_, MODE_) \
+  launch_rows_t<TO_, MODE_>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo)
+  if (pl.ra.k < 0)
+    launch_rows_k<int32_t, cs::ROWS_SUMS, 0, false>(pl, s, idx, lval, cnt, aug, bias, y, out, lo,
+                                                    geo);
+  else if (lo.idx != nullptr && ot == CS_I8) CS_ROWS(int8_t, cs::ROWS_LISTS);
+  else if (lo.idx != nullptr) CS_ROWS(int32_t, cs::ROWS_LISTS);
+  else if (ot == CS_I8) CS_ROWS(int8_t, cs::ROWS_DENSE);
+  else CS_ROWS(int32_t, cs::ROWS_DENSE);
+#undef CS_ROWS
   return launch_status();
 }
 
@@ -1567,7 +1590,7 @@ int cs_mrs_plan(cs_dtype xt, int cap, int b, int h, int w, int c_in, int kh, int
     info[0] = 5;
     info[6] = rp.blocks;
     info[7] = (int64_t)rp.shmem;
-    info[8] = rp.cpl;
+    info[8] = rp.cols;
     return CS_OK;
   }
   BlocksPlan bp;

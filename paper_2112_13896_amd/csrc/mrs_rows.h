@@ -3,29 +3,42 @@
 // convolution with stride 1, or a linear layer) with many items, each with a
 // short list and a row of 129-2048 outputs or a k over 32.
 //
-//  * the workgroup stages the packed table (value + Kernel ID per slot) in LDS
-//    once; after that its wavefronts work without workgroup barriers, each
-//    on its own items;
+//  * the workgroup stages the packed table (value and Kernel ID per slot, the
+//    ID already turned into the byte offset of its accumulator within the
+//    set) in LDS once; after that its wavefronts work without workgroup
+//    barriers, each on its own items;
 //  * a wavefront's accumulator row is in output-channel order and starts at
-//    the bias; lane j holds entry j of the item's list (its table row offset
-//    and value); when G > 32 each lane takes the sets g = lane + 64 q and the
-//    entries one after another (broadcast from their lanes), else the lanes
-//    form 64 / G slices of G sets, a slice taking every (64 / G)-th entry;
-//    a lane reads the table entry of (entry, set g), multiplies and adds the
-//    product to channel g*n + kid with an LDS integer add (exact in any
-//    order, so lanes may meet on one channel);
-//  * lane l then holds the CPL consecutive channels l*CPL, ... of the row in
-//    registers (CPL odd: the strided reads are free of bank conflicts), and the
-//    row's memory serves as a 512-bin histogram for an exact radix select of
-//    the k-th largest sum (9-bit digits of the sum minus the row minimum; keys
-//    outside the current prefix go to per-lane spare bins, so no lane is
-//    masked); ties go to the lower channel, winners are written in channel
-//    order; the lane then puts its bias back into the row for the next item.
+//    the bias; lane j holds entries j and j + 64 of the item's list (table row
+//    offset and value); sets in groups of 64 take the entries one after
+//    another (broadcast from their lanes), a rest of at most 32 sets as 64 /
+//    rest slices, a slice taking every (64 / rest)-th entry; a lane reads the
+//    table entry of (entry, set g), multiplies and adds the product to channel
+//    g*n + kid with an LDS integer add (exact in any order, so lanes may meet
+//    on one channel): three vector instructions a product, the multiply and
+//    the address add each selecting their byte of the entry;
+//  * k-WTA: lane l holds channels l, l + 64, ... of the row in registers, as
+//    differences from the row minimum, and the row's memory becomes a 512-bin
+//    histogram of their top nine bits; a scan from the top bin finds the bin of
+//    the k-th largest.  With a row's sums spread over the bins that bin holds a
+//    key or two: if all of it wins the threshold lies just below it, else a few
+//    keys are picked out one by one; only a crowded bin takes another
+//    histogram pass over nine more bits.  Ties go to the lower channel;
+//  * the winners' list positions are ballot ranks (channel order is column
+//    order, lane order within a column): a compare and a count of mask bits a
+//    column, no scans; the list is staged in the row's memory and copied out
+//    with consecutive lanes on consecutive entries, then the row is put back to
+//    the bias for the next item.
+//
+// What bounds it: the issue of a wavefront's serial chain (about 1,000
+// instructions an item, 440 of them vector, six to eight wavefronts a SIMD) and,
+// behind it, the LDS adds.  25,088 items, 96 -> 576 in sets of eight, 12 entries,
+// 72 winners as int8 lists: 46.1 -> 32.5 us (740 vector instructions an item
+// before: a full histogram pass per nine bits, list positions by scans over
+// strided lanes, an item loop compiled as divergent); the 576 -> 96 sums of the
+// same items 22.7 -> 17.2 us (72 entries in one piece instead of two).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-
-#include <type_traits>
 
 #include "fastdiv.h"
 #include "kwta_kernels.h"
@@ -36,10 +49,15 @@ namespace cs {
 
 constexpr int ROWS_BD = 1024;             // most threads per workgroup (16 wavefronts)
 constexpr int ROWS_BATCH = 4;             // table entries a lane reads before it adds
-constexpr int ROWS_ENT_STRIDE = 66;       // int2 slots per wavefront entry copy (64 + zero + pad)
-constexpr int ROWS_DIGIT = 9;             // bits per radix pass
+constexpr int ROWS_ENTS = 128;            // list entries held by a wavefront at a time
+constexpr int ROWS_ENT_STRIDE = ROWS_ENTS + 2;   // int2 slots per wavefront entry copy (+ zero + pad)
+constexpr int ROWS_DIGIT = 9;             // bits per histogram pass
 constexpr int ROWS_BINS = 1 << ROWS_DIGIT;
 constexpr int ROWS_HIST = ROWS_BINS + 64; // bins + one spare bin per lane
+constexpr int ROWS_STAGE = 4;             // 16-byte table loads of a thread in flight
+constexpr int ROWS_FEW = 16;              // list entries up to which a rest of sets runs as a group
+constexpr int ROWS_EXTRACT = 4;           // most winners of a bin picked out one by one
+constexpr int ROWS_BIN_KEYS = 16;         // ... from at most so many keys of the bin
 
 struct RowsArgs {
   int k;
@@ -49,15 +67,27 @@ struct RowsArgs {
   int S;              // slices of the remaining Gs sets (0: none)
   int gbase;          // first of the remaining sets (64 qf)
   uint32_t off_acc;    // LDS byte offset of the wavefronts' rows (table at 0)
-  uint32_t acc_words;  // words per wavefront row (>= c_out and >= ROWS_HIST)
-  uint32_t off_bias;   // LDS byte offset of the bias (c_out words)
-  uint32_t off_ent;    // LDS byte offset of the wavefronts' entry copies (S > 1 only)
+  uint32_t acc_words;  // words per wavefront row (whole columns, >= ROWS_HIST for a k-WTA)
+  uint32_t off_bias;   // LDS byte offset of the bias (whole 64-channel columns)
+  uint32_t off_ent;    // LDS byte offset of the wavefronts' entry copies (S > 0 only)
   int64_t per_wg;      // items per workgroup
   FastDiv fd_g;        // / Gs
 };
 
-template <typename TO, int CPL, bool FULL>
-__global__ __launch_bounds__(ROWS_BD) void mrs_rows(const uint16_t* __restrict__ lidx,
+// A staged table entry: the value in byte 0, the accumulator's byte offset
+// within its set (4 * kid <= 124) in byte 1.
+__device__ __forceinline__ uint32_t rows_entry2(uint32_t w) {       // two entries
+  return (w & 0x00FF00FFu) | ((w & 0x1F001F00u) << 2);
+}
+
+// What the kernel writes: the sums, the winners as lists, or densely.
+constexpr int ROWS_SUMS = 0, ROWS_LISTS = 1, ROWS_DENSE = 2;
+
+// M: 64-channel columns held by a lane (64 M >= c_out; 0 with ROWS_SUMS).
+// FULL: c_out == 64 M.
+// Registers held to eight wavefronts per SIMD up to nine columns.
+template <typename TO, int MODE, int M, bool FULL>
+__global__ __launch_bounds__(ROWS_BD, M <= 9 ? 8 : 4) void mrs_rows(const uint16_t* __restrict__ lidx,
                                                     const int8_t* __restrict__ lval,
                                                     const int32_t* __restrict__ lcnt,
                                                     const uint16_t* __restrict__ aug,
@@ -65,19 +95,21 @@ __global__ __launch_bounds__(ROWS_BD) void mrs_rows(const uint16_t* __restrict__
                                                     int32_t* __restrict__ y, TO* __restrict__ out,
                                                     ListOut lo, ConvGeom geo, RowsArgs ra,
                                                     int64_t items) {
-  static_assert(CPL % 2 == 1, "odd channels per lane keep the row reads conflict-free");
-  static_assert(CPL <= 64, "the winner mask holds 64 slots");
-  using Mask = typename std::conditional<(CPL > 32), uint64_t, uint32_t>::type;
   typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
   extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // the wavefront's number as a scalar: with it in a vector register the whole
+  // item loop is compiled as divergent (masks for branches, 64-bit addresses
+  // in vector registers)
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nthr = (int)blockDim.x, nwv = nthr >> 6;
   const int G = geo.G, n = geo.n, c = geo.c_out, cap = geo.cap;
   // the packed table [C][G] is at LDS offset 0
   int32_t* acc = reinterpret_cast<int32_t*>(smem + ra.off_acc) + wv * ra.acc_words;
-  uint32_t* hist = reinterpret_cast<uint32_t*>(acc);                      // the same words
-  int32_t* bias_s = reinterpret_cast<int32_t*>(smem + ra.off_bias);     // [c_out]
-  // (row offset, value) of up to 64 entries, then a (0, 0) entry for slots past the list
+  unsigned char* accb = reinterpret_cast<unsigned char*>(acc);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(acc);                // the same words
+  int32_t* bias_s = reinterpret_cast<int32_t*>(smem + ra.off_bias); // [64 cols]
+  // (row offset, value) of up to ROWS_ENTS entries, then a (0, 0) entry for slots past the list
   int2* ent = reinterpret_cast<int2*>(smem + ra.off_ent) + wv * ROWS_ENT_STRIDE;
 
   // ---- the table into LDS (16-byte pieces), once per workgroup
@@ -86,33 +118,46 @@ __global__ __launch_bounds__(ROWS_BD) void mrs_rows(const uint16_t* __restrict__
     const int n16 = nb / 16;
     const uint4* src = reinterpret_cast<const uint4*>(aug);
     uint4* dst = reinterpret_cast<uint4*>(smem);
-    for (int b0 = 0; b0 < n16; b0 += nthr * 4) {
-      uint4 v[4];
+    for (int b0 = 0; b0 < n16; b0 += nthr * ROWS_STAGE) {
+      uint4 v[ROWS_STAGE];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < ROWS_STAGE; ++u) {
         const int e = b0 + u * nthr + tid;
         v[u] = src[e < n16 ? e : n16 - 1];
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < ROWS_STAGE; ++u) {
         const int e = b0 + u * nthr + tid;
-        if (e < n16) dst[e] = v[u];
+        if (e < n16)
+          dst[e] = make_uint4(rows_entry2(v[u].x), rows_entry2(v[u].y), rows_entry2(v[u].z),
+                              rows_entry2(v[u].w));
       }
     }
-    for (int e = n16 * 16 + tid; e < nb; e += nthr)              // the tail bytes
-      smem[e] = reinterpret_cast<const unsigned char*>(aug)[e];
+    for (int e = n16 * 8 + tid; e < nb / 2; e += nthr)              // the tail entries
+      reinterpret_cast<uint16_t*>(smem)[e] = (uint16_t)rows_entry2(aug[e]);
   }
-  // the lane's channels ch0 .. ch0 + nv - 1 and their bias; rows start at the bias
-  const int ch0 = lane * CPL;
-  // FULL: c_out = 64 CPL, every lane's slots are channels
-  const int nv = FULL ? CPL : (c - ch0 < 0 ? 0 : (c - ch0 < CPL ? c - ch0 : CPL));
-  for (int o = tid; o < c; o += nthr) bias_s[o] = bias != nullptr ? bias[o] : 0;
-  if (lane == 0) ent[64] = make_int2(0, 0);
+  const int cols = (c + 63) >> 6;
+  for (int o = tid; o < 64 * cols; o += nthr) bias_s[o] = bias != nullptr && o < c ? bias[o] : 0;
+  if (ra.S > 0 && lane == 0) ent[ROWS_ENTS] = make_int2(0, 0);
   __syncthreads();
-  // a lane's slots past c_out (pads) take part as the row's smallest keys and
-  // never win; their row words are scratch
+  // columns past c_out are skipped (uniform); the last column's lanes past
+  // c_out are pads: words of their own, never in the histogram, never winners
+  // (c_out is made unknown again at each loop, or the comparisons would all be
+  // held in scalar registers across the item loop and spilled)
+  int cc = c;
+  auto has = [&](int j) { return FULL || 64 * j < cc; };
+  auto valid = [&](int j, int ln) { return FULL || 64 * j + ln < cc; };
+  auto reset_row = [&](int ln) {
+    if constexpr (MODE == ROWS_SUMS) {
+      for (int j = 0; j < cols; ++j) acc[64 * j + ln] = bias_s[64 * j + ln];
+    } else {
+      cc = opaque_uniform(c);
 #pragma unroll
-  for (int i = 0; i < CPL; ++i) acc[ch0 + i] = bias_s[ch0 + i < c ? ch0 + i : c - 1];
+      for (int j = 0; j < M; ++j)
+        if (has(j)) acc[64 * j + ln] = bias_s[64 * j + ln];
+    }
+  };
+  reset_row(lane);
 
   const int64_t ib = (int64_t)blockIdx.x * ra.per_wg;
   const int nit = (int)(items - ib < ra.per_wg ? items - ib : ra.per_wg);
@@ -122,89 +167,116 @@ __global__ __launch_bounds__(ROWS_BD) void mrs_rows(const uint16_t* __restrict__
   const int g0 = lane - s * (int)ra.fd_g.d;
   const bool job = s < ra.S;
 
-  // the next item's count and first 64 list entries (one per lane) are loaded while
-  // the current item is processed
+  // the next item's count and first 128 list entries (two per lane) are loaded
+  // while the current item is processed
   int cnt_n = 0;
-  uint16_t pi_n = 0;
-  int8_t pv_n = 0;
+  uint16_t pi_n[2] = {0, 0};
+  int8_t pv_n[2] = {0, 0};
   auto prefetch = [&](int li) {
     if (li < nit) {
       const int64_t it = ib + li;
       cnt_n = lcnt[it];
-      const int j = lane < cap ? lane : cap - 1;
-      pi_n = lidx[it * cap + j];
-      pv_n = lval[it * cap + j];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (64 * h < cap) {                                         // uniform
+          const int j = lane + 64 * h < cap ? lane + 64 * h : cap - 1;
+          pi_n[h] = lidx[it * cap + j];
+          pv_n[h] = lval[it * cap + j];
+        }
+      }
     }
+  };
+  auto add = [&](unsigned char* ag, uint32_t w, int x) {
+    __hip_atomic_fetch_add(reinterpret_cast<int32_t*>(ag + ((w >> 8) & 0xFFu)),
+                           __mul24(x, (int)(int8_t)(w & 0xFFu)), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
   };
   int li = wv;                                                      // uniform
   prefetch(li);
   while (li < nit) {
-    // the lane's first channel, recomputed per item (not held in registers per slot)
-    const int cl = opaque_int(ch0);
     const int lnext = li + nwv;
+    // (the lane's places are worked out per item, not held for every column)
+    const int lane = opaque_int(tid) & 63;
     const int64_t it = ib + li;
     int cnt = __builtin_amdgcn_readfirstlane(cnt_n);
     cnt = cnt < 0 ? 0 : (cnt > cap ? cap : cnt);
-    const uint16_t pi = pi_n;
-    const int8_t pv = pv_n;
+    uint16_t pi[2] = {pi_n[0], pi_n[1]};
+    int8_t pv[2] = {pv_n[0], pv_n[1]};
     prefetch(lnext);
 
     // ---- Multiply, Route, Sum
     const int64_t lb = it * cap;
-    for (int j0 = 0; j0 < cnt; j0 += 64) {                          // uniform
-      const int nb = cnt - j0 < 64 ? cnt - j0 : 64;
-      // lane j holds entry j0 + j: its table row's byte offset and its value
-      int pre, xv;
-      {
-        const int j = lane < nb ? lane : nb - 1;
-        const uint16_t ix = j0 == 0 ? pi : lidx[lb + j0 + j];
-        const int8_t v = j0 == 0 ? pv : lval[lb + j0 + j];
-        pre = (int)ix * G * 2;
-        xv = lane < nb ? (int)v : 0;
+    // a rest of sets runs as one more (partial) group when the list is short:
+    // a product in a group costs three instructions, the entry copy and the
+    // slices' reads of it about forty once and nine an entry slot
+    const bool group = ra.S > 0 && ra.qf > 0 && cnt <= ROWS_FEW;
+    const int qf = group ? ra.qf + 1 : ra.qf;
+    for (int j0 = 0; j0 < cnt; j0 += ROWS_ENTS) {                   // uniform
+      const int nb = cnt - j0 < ROWS_ENTS ? cnt - j0 : ROWS_ENTS;
+      // lane l holds entries j0 + l and j0 + l + 64: their table rows' byte
+      // offsets and their values (zero past the list)
+      int pre[2], xv[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int j = lane + 64 * h;
+        pre[h] = xv[h] = 0;
+        if (64 * h < nb) {                                          // uniform
+          if (j0 > 0) {
+            const int jc = j < nb ? j : nb - 1;
+            pi[h] = lidx[lb + j0 + jc];
+            pv[h] = lval[lb + j0 + jc];
+          }
+          pre[h] = j < nb ? (int)pi[h] * G * 2 : 0;
+          xv[h] = j < nb ? (int)pv[h] : 0;
+        }
       }
       // groups of 64 sets: lane l takes set 64 q + l, the entries one after
       // another (wavefront-uniform, read from their lanes)
-      for (int e = 0; ra.qf > 0 && e < nb; e += ROWS_BATCH) {       // uniform
-        int sp[ROWS_BATCH], sx[ROWS_BATCH];
+      if (qf > 0) {
 #pragma unroll
-        for (int u = 0; u < ROWS_BATCH; ++u) {
-          const int eu = e + u < nb ? e + u : nb - 1;
-          sp[u] = __builtin_amdgcn_readlane(pre, eu);
-          sx[u] = e + u < nb ? __builtin_amdgcn_readlane(xv, eu) : 0;
-        }
-        for (int q = 0; q < ra.qf; ++q) {                           // uniform
-          const int g = lane + 64 * q;
-          if (g < G) {                                              // all lanes but in a last partial group
-            CS_COUNT_PRODUCTS_ADD(min(ROWS_BATCH, nb - e));
-            uint32_t w[ROWS_BATCH];
+        for (int h = 0; h < 2; ++h) {
+          const int nh = nb - 64 * h < 64 ? nb - 64 * h : 64;
+          for (int e = 0; e < nh; e += ROWS_BATCH) {                // uniform
+            int sp[ROWS_BATCH], sx[ROWS_BATCH];
 #pragma unroll
-            for (int u = 0; u < ROWS_BATCH; ++u)
-              w[u] = *reinterpret_cast<const uint16_t*>(smem + sp[u] + 2 * g);
-            int32_t* ag = acc + g * n;
+            for (int u = 0; u < ROWS_BATCH; ++u) {                  // lanes past nh hold (0, 0)
+              sp[u] = __builtin_amdgcn_readlane(pre[h], e + u);
+              sx[u] = __builtin_amdgcn_readlane(xv[h], e + u);
+            }
+            auto group_add = [&](int g) {                           // this lane's set g
+              CS_COUNT_PRODUCTS_ADD(min(ROWS_BATCH, nh - e));
+              uint32_t w[ROWS_BATCH];
 #pragma unroll
-            for (int u = 0; u < ROWS_BATCH; ++u)
-              __hip_atomic_fetch_add(ag + (int)(w[u] >> 8),
-                                     __mul24(sx[u], (int)(int8_t)(w[u] & 0xFFu)),
-                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              for (int u = 0; u < ROWS_BATCH; ++u)
+                w[u] = *reinterpret_cast<const uint16_t*>(smem + sp[u] + 2 * g);
+              unsigned char* ag = accb + g * n * 4;
+#pragma unroll
+              for (int u = 0; u < ROWS_BATCH; ++u) add(ag, w[u], sx[u]);
+            };
+            // all lanes but in a last partial group
+            if (lane < G) group_add(lane);
+            for (int q = 1; q < qf; ++q)                            // uniform
+              if (lane + 64 * q < G) group_add(lane + 64 * q);
           }
         }
       }
       // the remaining Gs sets (from gbase on) as S slices: lane (s, g0) takes
       // set gbase + g0 and the entries s, s + S, ..., read from a
       // wavefront-private copy of the entries in LDS
-      if (ra.S > 0) {
-        ent[lane] = make_int2(pre, xv);
+      if (ra.S > 0 && !group) {
+        ent[lane] = make_int2(pre[0], xv[0]);
+        if (nb > 64) ent[lane + 64] = make_int2(pre[1], xv[1]);
         wave_lds_order();
         if (job) {
           const int S = ra.S;
           const int g = ra.gbase + g0;
-          int32_t* ag = acc + g * n;
+          unsigned char* ag = accb + g * n * 4;
           for (int e = 0; e < nb; e += S * ROWS_BATCH) {            // uniform
             int2 en[ROWS_BATCH];
 #pragma unroll
             for (int u = 0; u < ROWS_BATCH; ++u) {
               const int el = e + s + S * u;
-              en[u] = ent[el < nb ? el : 64];
+              en[u] = ent[el < nb ? el : ROWS_ENTS];
             }
             CS_COUNT_PRODUCTS_ADD(min(ROWS_BATCH, (nb - e - s + S - 1) / S));
             uint32_t w[ROWS_BATCH];
@@ -212,20 +284,17 @@ __global__ __launch_bounds__(ROWS_BD) void mrs_rows(const uint16_t* __restrict__
             for (int u = 0; u < ROWS_BATCH; ++u)
               w[u] = *reinterpret_cast<const uint16_t*>(smem + en[u].x + 2 * g);
 #pragma unroll
-            for (int u = 0; u < ROWS_BATCH; ++u)
-              __hip_atomic_fetch_add(ag + (int)(w[u] >> 8),
-                                     __mul24(en[u].y, (int)(int8_t)(w[u] & 0xFFu)),
-                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (int u = 0; u < ROWS_BATCH; ++u) add(ag, w[u], en[u].y);
           }
         }
         wave_lds_order();                                           // before the buffer is rewritten
       }
     }
+    wave_lds_order();
 
-    if (ra.k < 0) {
+    if constexpr (MODE == ROWS_SUMS) {
       // ---- sums only: the row to HBM (16-byte stores when c_out allows),
       // then back to the bias
-      wave_lds_order();
       if ((c & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0) {
         typedef int32_t i4_t __attribute__((ext_vector_type(4)));
         i4_t* y4 = reinterpret_cast<i4_t*>(y + it * c);
@@ -234,65 +303,73 @@ __global__ __launch_bounds__(ROWS_BD) void mrs_rows(const uint16_t* __restrict__
         for (int o = lane; o < c; o += 64) y[it * c + o] = acc[o];
       }
       wave_lds_order();
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) acc[cl + i] = bias_s[cl + i < c ? cl + i : c - 1];
+      reset_row(lane);
       li = lnext;
       continue;
-    }
+    } else {
 
-    // ---- the row into registers; its memory becomes the histogram
-    uint32_t key[CPL];
+    // ---- the row into registers (key: the difference from the row's
+    // minimum); its memory becomes the histogram
+    uint32_t key[M];
+    int32_t vmin = INT32_MAX, vmax = INT32_MIN;
+    cc = opaque_uniform(c);
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) key[i] = order_key(acc[cl + i]);
-    if (ra.write_sums) {
-#pragma unroll
-      for (int i = 0; i < CPL; ++i)
-        if (i < nv) y[it * c + cl + i] = (int32_t)(key[i] ^ 0x80000000u);
-    }
-    uint32_t kmn = 0xFFFFFFFFu, kmx = 0u;
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      if (i < nv) {
-        kmn = key[i] < kmn ? key[i] : kmn;
-        kmx = key[i] > kmx ? key[i] : kmx;
+    for (int j = 0; j < M; ++j) {
+      if (has(j)) {
+        const int32_t v = acc[64 * j + lane];
+        key[j] = (uint32_t)v;
+        if (valid(j, lane)) {
+          if (ra.write_sums) y[it * c + 64 * j + lane] = v;
+          vmin = v < vmin ? v : vmin;
+          vmax = v > vmax ? v : vmax;
+        }
       }
     }
-    kmn = wave_min_u32(kmn);
-    kmx = wave_max_u32(kmx);
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) key[i] = i < nv ? key[i] - kmn : 0u;   // pads: 0
+    // (order keys: the unsigned reductions of the wavefront)
+    const uint32_t kmn = wave_min_u32(order_key(vmin)), kmx = wave_max_u32(order_key(vmax));
     const uint32_t range = kmx - kmn;
+    const uint32_t vbase = kmn ^ 0x80000000u;                       // the minimum's bits
+    cc = opaque_uniform(c);
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+      if (has(j)) key[j] -= vbase;
     const int k = ra.k;
-    uint32_t thr = 0u;                                              // an offset key
+    // winners: key > thr, and the first `need` keys (lowest channels) == thr
+    uint32_t thr = 0u;
     int need = 0;
     if (k <= 0) {
       thr = 0xFFFFFFFFu;
     } else if (k >= c) {
-      need = c;
+      need = c;                                                     // every key >= 0 wins
     } else if (range == 0u) {
       need = k;
     } else {
-      int rem = 32 - __builtin_clz(range);
-      int passes = (rem + ROWS_DIGIT - 1) / ROWS_DIGIT;
-      uint32_t prefix = 0u;
-      int nd = k;
+      int rem = 32 - __builtin_clz(range);                          // bits not yet resolved
+      uint32_t prefix = 0u;                                         // the bits above them
+      int nd = k;                                                   // winners among the prefix's keys
       const u4_t z = {0u, 0u, 0u, 0u};
-      wave_lds_order();                                             // the row reads first
-      reinterpret_cast<u4_t*>(hist)[2 * lane] = z;
-      reinterpret_cast<u4_t*>(hist)[2 * lane + 1] = z;
-      const int spare = ROWS_BINS + lane;
-      for (; passes > 0; --passes) {                                // uniform
-        const int width = (rem + passes - 1) / passes;
+      for (bool first = true;; first = false) {                     // uniform
+        const int width = rem < ROWS_DIGIT ? rem : ROWS_DIGIT;
         const int sh = rem - width;
-        const uint32_t hi = rem >= 32 ? 0u : (0xFFFFFFFFu << rem);
-        const uint32_t lob = rem >= 32 ? 0u : (prefix << rem);
+        wave_lds_order();                                           // the row (or bins) read
+        reinterpret_cast<u4_t*>(hist)[lane] = z;
+        reinterpret_cast<u4_t*>(hist)[64 + lane] = z;
         wave_lds_order();
+        const int spare = ROWS_BINS + lane;
+        const uint32_t dmask = (1u << width) - 1u;
+        cc = opaque_uniform(c);
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-          const bool in = (key[i] & hi) == lob;
-          const int bin = in ? (int)__builtin_amdgcn_ubfe(key[i], (uint32_t)sh, (uint32_t)width)
-                             : spare;
-          __hip_atomic_fetch_add(hist + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int j = 0; j < M; ++j) {
+          if (has(j)) {
+            int bin;
+            if (first) {
+              bin = valid(j, lane) ? (int)(key[j] >> sh) : spare;
+            } else {
+              const bool in = valid(j, lane) && (key[j] >> rem) == prefix;   // rem < 32 here
+              bin = in ? (int)((key[j] >> sh) & dmask) : spare;
+            }
+            __hip_atomic_fetch_add(hist + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
         }
         wave_lds_order();
         // lane l holds bins 8(63 - l) .. 8(63 - l) + 7: an inclusive scan over
@@ -300,113 +377,154 @@ __global__ __launch_bounds__(ROWS_BD) void mrs_rows(const uint16_t* __restrict__
         const int b0 = 8 * (63 - lane);
         const u4_t h0 = reinterpret_cast<const u4_t*>(hist + b0)[0];
         const u4_t h1 = reinterpret_cast<const u4_t*>(hist + b0)[1];
-        reinterpret_cast<u4_t*>(hist + b0)[0] = z;                  // the next pass's bins
-        reinterpret_cast<u4_t*>(hist + b0)[1] = z;
-        const uint32_t hb[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
-        int ls = 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) ls += (int)hb[q];
+        const int ls = (int)((h0.x + h0.y) + (h0.z + h0.w) + (h1.x + h1.y) + (h1.z + h1.w));
         const int incl = (int)wave_incl_scan((uint32_t)ls, 0u, OpAdd{});
-        const int above = incl - ls;
-        int run = above, bin = b0, found = 0;
-#pragma unroll
-        for (int q = 7; q >= 0; --q) {
-          const bool hit = !found && run + (int)hb[q] >= nd;
-          bin = hit ? b0 + q : bin;
-          run = (!found && !hit) ? run + (int)hb[q] : run;
-          found |= hit;
-        }
-        const uint64_t fb = __ballot(above < nd && nd <= incl);     // exactly one lane
+        const uint64_t fb = __ballot(incl >= nd);                   // not empty: nd <= the prefix's keys
         const int f = __ffsll((unsigned long long)fb) - 1;
-        prefix = (prefix << width) | (uint32_t)__builtin_amdgcn_readlane(bin, f);
-        nd -= __builtin_amdgcn_readlane(run, f);
+        const int above = __builtin_amdgcn_readlane(incl - ls, f);
+        // the eight bins of that lane, highest first, in lanes 0..7
+        const int bl = 8 * (63 - f) + 7 - (lane & 7);
+        const int hb = (int)hist[bl];
+        int run = hb;
+        run += __builtin_amdgcn_update_dpp(0, run, 0x111, 0xF, 0xF, false);
+        run += __builtin_amdgcn_update_dpp(0, run, 0x112, 0xF, 0xF, false);
+        run += __builtin_amdgcn_update_dpp(0, run, 0x114, 0xF, 0xF, false);
+        const uint64_t gb = __ballot(above + run >= nd);            // lanes 0..7: not empty
+        const int p = __ffsll((unsigned long long)gb) - 1;
+        const int m = __builtin_amdgcn_readlane(hb, p);             // keys of the bin
+        nd -= above + __builtin_amdgcn_readlane(run, p) - m;        // of them that win, 1 .. m
+        prefix = (prefix << width) | (uint32_t)(8 * (63 - f) + 7 - p);
         rem = sh;
-      }
-      thr = prefix;
-      need = nd;
-    }
-    // ---- winners in channel order: key > thr, or key == thr among the first `need`
-    int gt_l = 0, eq_l = 0;
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      gt_l += key[i] > thr ? 1 : 0;
-      eq_l += key[i] == thr ? 1 : 0;
-    }
-    const uint32_t pk = (uint32_t)eq_l | ((uint32_t)gt_l << 16);
-    const uint32_t pincl = wave_incl_scan(pk, 0u, OpAdd{});
-    int eqb = (int)((pincl - pk) & 0xFFFFu);                        // ties in lower lanes
-    // the list of the non-zero winners staged in the row's memory (positions
-    // in channel order, the other slots to spare entries k + lane) and copied
-    // out with consecutive lanes on consecutive entries, when it fits there
-    const int sidx_b = ((k + 64) * 2 + 3) & ~3;
-    const bool stage = lo.idx != nullptr && k >= 0 &&
-                       sidx_b + (k + 64) * (int)sizeof(TO) <= 4 * (int)ra.acc_words;
-    if (lo.idx) {
-      // the non-zero winners: counted first (bit i of pb), then written at
-      // their list positions
-      Mask pb = 0;
-      int np = 0, er = eqb;
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-        const bool eq = key[i] == thr;
-        const bool win = i < nv && (key[i] > thr || (eq && er < need));
-        er += eq ? 1 : 0;
-        const TO ov = kwta_out<int32_t, TO>((int32_t)((key[i] + kmn) ^ 0x80000000u), ra.shift);
-        const bool put = win && ov != TO(0);
-        pb |= put ? (Mask(1) << i) : Mask(0);
-        np += put ? 1 : 0;
-      }
-      const int pin = (int)wave_incl_scan((uint32_t)np, 0u, OpAdd{});
-      uint32_t pos = (uint32_t)(pin - np);
-      // row base pointers (uniform) and 32-bit byte offsets per lane
-      unsigned char* lv = reinterpret_cast<unsigned char*>(static_cast<TO*>(lo.val) + it * lo.cap);
-      unsigned char* lx = reinterpret_cast<unsigned char*>(lo.idx + it * lo.cap);
-      if (stage) {
-        uint16_t* sx = reinterpret_cast<uint16_t*>(acc);
-        TO* sv = reinterpret_cast<TO*>(reinterpret_cast<unsigned char*>(acc) + sidx_b);
-        wave_lds_order();                                           // after the histogram reads
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-          const bool put = (pb >> i) & Mask(1);
-          const int p = put ? (int)pos : k + lane;
-          sx[p] = (uint16_t)(cl + i);
-          sv[p] = kwta_out<int32_t, TO>((int32_t)((key[i] + kmn) ^ 0x80000000u), ra.shift);
-          pos += put ? 1u : 0u;
+        if (m == nd) {                  // the whole bin wins (not the lowest bin: k < c)
+          thr = (prefix << rem) - 1u;
+          break;
         }
-        wave_lds_order();
-        const int total = __builtin_amdgcn_readlane(pin, 63);
-        for (int j = lane; j < total; j += 64) {
-          *reinterpret_cast<uint16_t*>(lx + 2u * (uint32_t)j) = sx[j];
-          *reinterpret_cast<TO*>(lv + (uint32_t)sizeof(TO) * (uint32_t)j) = sv[j];
+        if (rem == 0) {                                             // one value, some of its copies win
+          thr = prefix;
+          need = nd;
+          break;
         }
-        wave_lds_order();                                           // before the row is reset
-      } else {
+        if (nd <= ROWS_EXTRACT && m <= ROWS_BIN_KEYS) {
+          // the bin's keys one after another into a sorted list of its largest
+          // (scalars; key - base + 1, so 0 is no key)
+          const uint32_t base = prefix << rem;
+          uint32_t top[ROWS_EXTRACT + 1] = {0u};
+          cc = opaque_uniform(c);
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-          if ((pb >> i) & Mask(1)) {
-            *reinterpret_cast<uint16_t*>(lx + 2u * pos) = (uint16_t)(cl + i);
-            *reinterpret_cast<TO*>(lv + (uint32_t)sizeof(TO) * pos) =
-                kwta_out<int32_t, TO>((int32_t)((key[i] + kmn) ^ 0x80000000u), ra.shift);
-            ++pos;
+          for (int j = 0; j < M; ++j) {
+            if (has(j)) {
+              const uint32_t d = key[j] - base;                     // below the bin: wraps high
+              uint64_t in = __ballot(valid(j, lane) && d < (1u << rem));
+              while (in != 0ull) {                                  // uniform, m rounds in all
+                const int l = __ffsll((unsigned long long)in) - 1;
+                in &= in - 1ull;
+                uint32_t x = 1u + (uint32_t)__builtin_amdgcn_readlane((int)d, l);
+#pragma unroll
+                for (int t = 0; t <= ROWS_EXTRACT; ++t) {
+                  const uint32_t hi = top[t] > x ? top[t] : x;
+                  x = top[t] > x ? x : top[t];
+                  top[t] = hi;
+                }
+              }
+            }
+          }
+          uint32_t val = top[0], next = top[1];                     // the nd-th and the one after
+          int gt = 0;
+#pragma unroll
+          for (int t = 1; t < ROWS_EXTRACT; ++t) {
+            val = t < nd ? top[t] : val;
+            next = t < nd ? top[t + 1] : next;
+          }
+#pragma unroll
+          for (int t = 0; t < ROWS_EXTRACT; ++t) gt += top[t] > val ? 1 : 0;
+          const bool split = next == val;                           // copies of it that lose
+          thr = base + val - (split ? 1u : 2u);                     // (not below 0: k < c)
+          need = split ? nd - gt : 0;
+          break;
+        }
+      }
+    }
+    // ---- winners in channel order, at list positions counted by ballots
+    int total = 0;
+    wave_lds_order();                                               // after the histogram reads
+    uint16_t* gx = nullptr;
+    TO* gv = nullptr;
+    if constexpr (MODE == ROWS_LISTS) {
+      gx = lo.idx + it * lo.cap;
+      gv = static_cast<TO*>(lo.val) + it * lo.cap;
+    }
+    // list position of a column's winner: the winners of the columns before
+    // and of the lanes before
+    auto rank = [&](uint64_t mask, int before) {
+      return (int)__builtin_amdgcn_mbcnt_hi(
+          (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)before));
+    };
+    // the keys and channels of the winners staged in the row's memory, then
+    // requantised and written with consecutive lanes on consecutive entries:
+    // when they fit there, no tie is split and no winner's output can be zero
+    // (the least winner, thr + 1, is at least 2^shift)
+    const uint32_t off_ch = ((uint32_t)k * 4 + 15) & ~15u;
+    bool fast = false;
+    if constexpr (MODE == ROWS_LISTS) {
+      const int64_t least = (int64_t)(int32_t)vbase + (int64_t)thr + 1;
+      fast = need == 0 && least >= (sizeof(TO) == 1 ? (int64_t)1 << ra.shift : (int64_t)1) &&
+             off_ch + 2u * (uint32_t)k <= 4u * ra.acc_words;
+    }
+    if (fast) {                                                     // uniform
+      uint16_t* sch = reinterpret_cast<uint16_t*>(accb + off_ch);
+      cc = opaque_uniform(c);
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        if (has(j)) {
+          const bool win = valid(j, lane) && key[j] > thr;
+          const uint64_t wb = __ballot(win);
+          const int pos = rank(wb, total);
+          if (win) {
+            hist[pos] = key[j];
+            sch[pos] = (uint16_t)(64 * j + lane);
+          }
+          total += __popcll(wb);
+        }
+      }
+      wave_lds_order();
+      for (int q = lane; q < total; q += 64) {
+        gx[q] = sch[q];
+        gv[q] = kwta_out<int32_t, TO>((int32_t)(hist[q] + vbase), ra.shift);
+      }
+    } else {
+      int ties = 0;
+      cc = opaque_uniform(c);
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        if (has(j)) {
+          const bool eq = need > 0 && valid(j, lane) && key[j] == thr;
+          const uint64_t eb = __ballot(eq);
+          const bool win = (valid(j, lane) && key[j] > thr) || (eq && rank(eb, ties) < need);
+          ties += __popcll(eb);
+          const TO ov = kwta_out<int32_t, TO>((int32_t)(key[j] + vbase), ra.shift);
+          if constexpr (MODE == ROWS_LISTS) {
+            const bool put = win && ov != TO(0);
+            const uint64_t pb = __ballot(put);
+            const int pos = rank(pb, total);
+            if (put) {
+              gx[pos] = (uint16_t)(64 * j + lane);
+              gv[pos] = ov;
+            }
+            total += __popcll(pb);
+          } else {
+            if (valid(j, lane)) out[it * c + 64 * j + lane] = win ? ov : TO(0);
           }
         }
       }
-      if (lane == 63) lo.cnt[it] = pin;
-    } else {
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-        const bool eq = key[i] == thr;
-        const bool win = key[i] > thr || (eq && eqb < need);
-        eqb += eq ? 1 : 0;
-        const TO ov = kwta_out<int32_t, TO>((int32_t)((key[i] + kmn) ^ 0x80000000u), ra.shift);
-        if (i < nv) out[it * c + cl + i] = win ? ov : TO(0);
-      }
+    }
+    if constexpr (MODE == ROWS_LISTS) {
+      if (lane == 0) lo.cnt[it] = total;
     }
     // ---- the row back to the bias for the next item
     wave_lds_order();
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) acc[cl + i] = bias_s[cl + i < c ? cl + i : c - 1];
+    reset_row(lane);
     li = lnext;
+    }
   }
 }
 

@@ -79,4 +79,10 @@ __device__ __forceinline__ int opaque_int(int v) {
   return v;
 }
 
+// The same for a wavefront-uniform value (a scalar register).
+__device__ __forceinline__ int opaque_uniform(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
 }  // namespace cs

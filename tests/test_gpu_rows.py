@@ -1,0 +1,91 @@
+"""The row kernel (one wavefront per item, int8 1x1 layers) where its selection
+and its list positions can go wrong: rows of one to thirty-two 64-channel
+columns with and without pads, a bin that holds the whole row (an outlier
+stretches the range), equal sums in and out of the winners, a row spanning the
+whole 32-bit range, winners that requantise to zero, lists longer than one
+and two 64-entry pieces, few and many entries over a rest of sets, k = 0 and
+k = c_out.  Sums, winners, values and lists equal the oracle's exactly.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import cs_oracle as o
+from paper_2112_13896_amd import ops
+from tests.gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+# items, c_in, non-zeros, c_out, n, k, shift, form, data
+CASES = [
+    (300, 96, 12, 576, 8, 72, 9, "lists", "plain"),      # the expand shape; whole columns
+    (300, 96, 12, 576, 8, 72, 9, "lists", "outlier"),    # every key but one in one bin
+    (300, 96, 12, 576, 8, 72, 0, "lists", "ties"),       # few distinct sums
+    (300, 96, 12, 576, 8, 72, 12, "lists", "plain"),     # some winners requantise to zero
+    (300, 96, 17, 576, 8, 72, 9, "dense", "plain"),      # one entry past the short-list rule
+    (200, 64, 8, 192, 16, 40, None, "lists", "wide"),    # int32 lists, 32-bit range
+    (200, 64, 8, 130, 2, 33, 5, "lists", "wide"),        # pads: 130 channels of 192
+    (130, 200, 200, 384, 8, 384, None, "dense", "plain"),   # 200 entries, k = c_out
+    (130, 200, 140, 320, 8, 0, 9, "lists", "plain"),     # k = 0
+    (500, 160, 20, 960, 8, 120, 9, "lists", "plain"),    # 15 columns
+    (150, 40, 6, 2048, 16, 700, 6, "lists", "ties"),     # 32 columns, lists past the staging
+    (150, 72, 70, 1000, 20, 5, None, "dense", "outlier"),
+    (128, 96, 12, 136, 8, 34, 9, "lists", "equal"),      # every sum equal
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"{c[3]}-k{c[5]}-{c[7]}-{c[8]}" for c in CASES])
+def test_rows_match_oracle(case):
+    items, c_in, nnz, c_out, n, k, shift, form, data = case
+    r = np.random.default_rng(items + c_out + k)
+    x = np.zeros((items, c_in), np.int8)
+    for i in range(items):
+        at = r.permutation(c_in)[:nnz if i % 7 else nnz // 2]          # ragged counts
+        x[i, at] = 1 if data in ("ties", "equal") else r.integers(1, 128, len(at))
+    x[items // 3] = 0                                                  # an empty row
+    G = c_out // n
+    kid = r.integers(0, n, (G, c_in))                                  # each slot's kernel
+    v = r.integers(1, 128, (G, c_in)) * r.choice([-1, 1], (G, c_in))
+    if data == "ties":
+        v = np.sign(v)
+    W = np.zeros((G, n, c_in), np.int8)
+    if data != "equal":
+        np.put_along_axis(W, kid[:, None, :], v[:, None, :].astype(np.int8), axis=1)
+    W = W.reshape(c_out, c_in)
+    bias = r.integers(-1000, 1001, c_out).astype(np.int64)
+    if data == "outlier":
+        bias[c_out // 2] = 2**30
+    elif data == "wide":
+        bias[::5] = 2**31 - 2**20
+        bias[1::5] = -2**31 + 2**20
+    elif data in ("ties", "equal"):
+        bias[:] = 300
+    bias = bias.astype(np.int32)
+    aug = ops.aug_to_device(ops.pack(W, n)[0])
+    shape = (1, items, 1, c_in)
+    assert ops.mrs_plan(torch.int8, c_in, shape, 1, 1, 1, 0, c_out, n, 1, k)["path"] == "rows"
+    idx, lv, cnt = ops.compact(dev(x))
+    ref = o.linear(x, W, bias)
+    win = o.kwta_winners(ref, k)
+    want = np.where(win, ref, 0) if shift is None else o.requant(ref, shift, win)
+    odt = torch.int8 if shift is not None else None
+    for keep in (True, False):
+        y, got = ops.mrs_kwta_conv2d(idx, lv, cnt, shape, aug, 1, 1, n, bias=dev(bias), k=k,
+                                     out_dtype=odt, shift=shift or 0, keep_sums=keep,
+                                     cap=ops.list_capacity(k) if form == "lists" else None)
+        if keep:
+            assert np.array_equal(host(y).reshape(items, c_out).astype(np.int64), ref)
+        if form == "dense":
+            assert np.array_equal(host(got).reshape(items, c_out).astype(np.int64), want)
+            continue
+        gi, gv, gc = (host(t) for t in got)
+        assert np.array_equal(gc, (want != 0).sum(axis=1))
+        for i in range(items):
+            nz = np.flatnonzero(want[i])
+            assert np.array_equal(gi[i, :gc[i]].view(np.uint16), nz)
+            assert np.array_equal(gv[i, :gc[i]].astype(np.int64), want[i, nz])
+    # the sums alone
+    y = ops.mrs_conv2d(idx, lv, cnt, shape, aug, 1, 1, n, bias=dev(bias))
+    assert np.array_equal(host(y).reshape(items, c_out).astype(np.int64), ref)

@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void compact_narrow(const T* __restrict__ x, i
 
 // Rows whose length is a multiple of E = 16 / sizeof(T) elements (16-byte
 // rows, 16-byte aligned base): each lane loads E consecutive elements with one
-// 16-byte load.  A row takes NL = c / E lanes; rows of NL <= 16 lanes are
+// 16-byte load.  A row takes NL = c / E lanes; rows of NL <= 32 lanes are
 // packed 64 / L to a wavefront in aligned groups of L = NL rounded up to a
 // power of two, longer rows take a whole wavefront each and go through the
 // row 64 vectors at a time.  A lane loads only when its row exists and its
@@ -128,9 +128,14 @@ struct Vec16<int8_t> {
   }
 };
 
-// Inclusive prefix sum over aligned groups of 1 << lg lanes (lg <= 4, one DPP
-// row) or the whole wavefront (lg == 6); p = the lane's place in its group.
+// Inclusive prefix sum over aligned groups of 1 << lg lanes (lg <= 4: in one
+// DPP row; 5: two rows, the first one's total broadcast to the second) or the
+// whole wavefront (lg == 6); p = the lane's place in its group.
 __device__ __forceinline__ int compact_group_incl(int v, int lg, int p) {
+  if (lg == 5) {
+    v = row16_incl_sum(v);
+    return v + __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+  }
   if (lg == 6) return (int)wave_incl_scan((uint32_t)v, 0u, OpAdd{});
   if (lg >= 1) { const int t = __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false); v += p >= 1 ? t : 0; }
   if (lg >= 2) { const int t = __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false); v += p >= 2 ? t : 0; }
@@ -139,7 +144,11 @@ __device__ __forceinline__ int compact_group_incl(int v, int lg, int p) {
   return v;
 }
 
-// lg: log2 of the lanes per row group (0..4, or 6: one row per wavefront).
+// lg: log2 of the lanes per row group (0..5, or 6: one row per wavefront).
+// Two rows of 17 to 32 vectors share a wavefront: 40,768 rows of 128 fp32 took
+// 9.8 us with one row and half the lanes idle, 8.6 us with two.  (A row of
+// several passes with four vectors per lane loaded ahead measured the other way,
+// 12.1 -> 14.1 us at 12,544 rows of 1024: the passes are bound by their stores.)
 template <typename T>
 __global__ __launch_bounds__(256) void compact_vec(const T* __restrict__ x, int64_t rows, int c,
                                                    int lg, uint16_t* __restrict__ idx,

@@ -60,14 +60,14 @@ int blocks_for(int64_t threads, int bd, int64_t cap = 1 << 20) {
 int device_cus(int* cus);
 
 // The vectorised compaction's lanes per row group (log2): 16-byte rows of at
-// most 16 vectors share a wavefront in power-of-two groups, longer ones take a
+// most 32 vectors share a wavefront in power-of-two groups, longer ones take a
 // wavefront each; -1 when the rows are not whole 16-byte vectors or x is not
 // 16-byte aligned.
 int compact_vec_lg(cs_dtype xt, const void* x, int c) {
   const int E = xt == CS_I8 ? 16 : 4;
   if (c % E != 0 || reinterpret_cast<uintptr_t>(x) % 16 != 0) return -1;
   const int nl = c / E;
-  if (nl > 16) return 6;
+  if (nl > 32) return 6;
   int lg = 0;
   while ((1 << lg) < nl) ++lg;
   return lg;

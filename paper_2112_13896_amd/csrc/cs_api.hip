@@ -25,6 +25,7 @@
 #include "mrs_sample.h"
 #include "mrs_rows.h"
 #include "mrs_scatter.h"
+#include "mrs_stream.h"
 #include "mrs_tiled.h"
 
 // Scratch of cs_conv2d_noalloc: the compaction lists it would otherwise take
@@ -719,6 +720,112 @@ int launch_blocks(const BlocksPlan& pl, hipStream_t stream, const uint16_t* idx,
   return launch_status();
 }
 
+// ------------------------------------- fp32 layers, table streamed through LDS
+struct StreamPlan {
+  cs::StreamArgs sa;
+  int gb, kp, threads;
+  int64_t blocks;
+  size_t shmem;
+};
+
+// The layers that blocks_plan takes whose table does not stay in LDS, when a
+// pixel's channels divide into 4, 8 or 16 lanes of 8 or 16 channels: measured
+// faster than the table-block kernel at every such layer tried (14x14x256 3x3,
+// 64 images, 41.7 -> 36.2 us; 1x1 1024 -> 256 33.0 -> 27.1 us; 56x56x128 3x3/2, 13
+// images, 28.4 -> 20.8 us).  cus: compute units of the device, or 0 when only
+// planning.  unit: as blocks_plan.
+bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const void* y,
+                 const void* out, int k, int write_sums, int cus, StreamPlan* pl, int unit = 0) {
+  if (xt != CS_F32 || geo.pool != 1) return false;
+  if (unit <= 0) unit = geo.c_out;
+  const int n = geo.n, G = geo.G;
+  const int log2n = ilog2_exact(n), log2G = ilog2_exact(G);
+  if (log2n < 0 || log2G < 2 || geo.c_out > 256) return false;
+  if (geo.cap % 4 != 0 || !aligned(aug, 16) || !aligned(y, 16) || !aligned(out, 16)) return false;
+  const int T = geo.KH * geo.KW;
+  const int64_t R = (int64_t)T * geo.C;
+  const int64_t items = (int64_t)geo.B * geo.Ho * geo.Wo;
+  const int64_t in_rows = (int64_t)geo.B * geo.H * geo.W;
+  if (items * geo.c_out >= INT32_MAX || in_rows * geo.cap >= INT32_MAX || R * G >= INT32_MAX)
+    return false;
+  const int gb = G > 16 ? G / 16 : 1;
+  const int kp = gb * n, U = G / gb;
+  if (gb > 2 || (kp != 8 && kp != 16)) return false;
+  const int64_t row_b = (int64_t)G * 8;
+  // a table that stays in LDS next to a workgroup's accumulators: blocks_plan
+  if ((int64_t)2 * n * cs::BLK_BD * 4 + R * row_b <= (int64_t)(kCuLds / 2)) return false;
+  cs::StreamArgs& sa = pl->sa;
+  const int max_rows = (int)(cs::STREAM_BLOCK / row_b);
+  int64_t RB = 0;
+  sa.tpb = 0;
+  sa.cblocks = 0;
+  if (geo.C <= max_rows) {
+    sa.tpb = std::min(max_rows / geo.C, T);
+    RB = (int64_t)sa.tpb * geo.C;
+  } else {
+    RB = max_rows;
+    while (RB >= 4 && geo.C % RB != 0) --RB;
+    if (RB < 4) return false;
+    sa.cblocks = (int)(geo.C / RB);
+  }
+  sa.log2U = ilog2_exact(U);
+  sa.items = (int)items;
+  sa.RB = (int)RB;
+  sa.nblocks = (int)((R + RB - 1) / RB);
+  sa.log2n = log2n;
+  sa.log2G = log2G;
+  sa.k = k;
+  sa.write_sums = write_sums;
+  const int log2Us = unit % kp == 0 ? ilog2_exact(unit / kp) : -1;
+  if (log2Us < 0 || log2Us > sa.log2U) return false;
+  sa.log2Us = log2Us;
+  const size_t tb = ((size_t)RB * row_b + cs::STREAM_PIECE - 1) / cs::STREAM_PIECE * cs::STREAM_PIECE;
+  sa.off_t0 = (uint32_t)kp * cs::STREAM_BD * 4;
+  sa.off_t1 = sa.off_t0 + (sa.nblocks > 1 ? (uint32_t)tb : 0u);
+  sa.table_bytes = R * row_b;
+  sa.fd_wo = cs::make_fastdiv((uint32_t)geo.Wo);
+  sa.fd_ho = cs::make_fastdiv((uint32_t)geo.Ho);
+  sa.fd_kw = cs::make_fastdiv((uint32_t)geo.KW);
+  // one workgroup per compute unit at a time: the fewest rounds over the
+  // compute units, and in them the fewest wavefronts a workgroup (at least four,
+  // which share the table's copies)
+  const int ppw = 64 / U, units = cus > 0 ? cus : kPlanCus;
+  const int64_t rounds = (items + (int64_t)units * 16 * ppw - 1) / ((int64_t)units * 16 * ppw);
+  int64_t waves = (items + rounds * units * ppw - 1) / (rounds * units * ppw);
+  waves = waves < 4 ? 4 : waves;
+  sa.P = (int)waves * ppw;
+  pl->threads = (int)waves * 64;
+  pl->blocks = (items + sa.P - 1) / sa.P;
+  pl->gb = gb;
+  pl->kp = kp;
+  pl->shmem = (size_t)sa.off_t1 + tb;
+  return pl->shmem <= kCuLds && pl->blocks < INT32_MAX;
+}
+
+int launch_stream(const StreamPlan& pl, hipStream_t stream, const uint16_t* idx, const void* lval,
+                  const int32_t* cnt, const void* aug, const void* bias, void* y, void* out,
+                  const cs::ListOut& lo, const cs::ConvGeom& geo) {
+#define CS_STREAM(GB_, CH_, KP_)                                                             \
+  hipLaunchKernelGGL((cs::mrs_stream_f32<float, GB_, CH_, KP_>), dim3((unsigned)pl.blocks),   \
+                     dim3(pl.threads), pl.shmem, stream, idx, static_cast<const float*>(lval), \
+                     cnt, static_cast<const uint2*>(aug), static_cast<const float*>(bias),    \
+                     static_cast<float*>(y), static_cast<float*>(out), lo, geo, pl.sa)
+#define CS_STREAM_KP(GB_, CH_)              \
+  do {                                      \
+    if (pl.kp == 8) CS_STREAM(GB_, CH_, 8); \
+    else CS_STREAM(GB_, CH_, 16);           \
+  } while (0)
+  const bool ch = pl.sa.tpb == 0;
+  if (pl.gb == 1) {
+    if (ch) CS_STREAM_KP(1, true); else CS_STREAM_KP(1, false);
+  } else {
+    if (ch) CS_STREAM_KP(2, true); else CS_STREAM_KP(2, false);
+  }
+#undef CS_STREAM_KP
+#undef CS_STREAM
+  return launch_status();
+}
+
 // ------------------------------------------------ one sample per workgroup
 // A layer whose output is one vector per sample (a linear layer, or a
 // convolution whose window is the whole unpadded input map) runs with one
@@ -1147,9 +1254,14 @@ int mrs_launch(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t
     int cus = 0;
     const int dst = device_cus(&cus);
     if (dst != CS_OK) return dst;
-    if (blocks_plan(geo, xt, aug, y, nullptr, -1, 1, 0, false, cus, &bp))
+    if (blocks_plan(geo, xt, aug, y, nullptr, -1, 1, 0, false, cus, &bp)) {
+      StreamPlan tp;
+      if (stream_plan(geo, xt, aug, y, nullptr, -1, 1, cus, &tp))
+        return launch_stream(tp, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                             cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
       return launch_blocks(bp, stream, idx, lval, cnt, aug, bias, y, nullptr,
                            cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
+    }
     FusedPlan fp;
     if (fused_plan(geo, xt, aug, y, -1, 0, 1, 0, 0, &fp))
       return launch_fused(fp, xt, xt, stream, idx, lval, cnt, aug, bias, y, nullptr,
@@ -1490,8 +1602,12 @@ int cs_mrs_kwta_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval, const
       const int dst = device_cus(&cus);
       if (dst != CS_OK) return dst;
     }
-    if (blocks_plan(geo, xt, aug, y, out, k, keep_sums, lists ? ocap : 0, lvec, cus, &bp))
+    if (blocks_plan(geo, xt, aug, y, out, k, keep_sums, lists ? ocap : 0, lvec, cus, &bp)) {
+      StreamPlan tp;
+      if (stream_plan(geo, xt, aug, y, out, k, keep_sums, cus, &tp))
+        return launch_stream(tp, s, idx, lval, cnt, aug, bias, y, out, lo, geo);
       return launch_blocks(bp, s, idx, lval, cnt, aug, bias, y, out, lo, geo);
+    }
   }
   if (lists_ok && lists_vectorisable(xt, idx, lval, cap)) {
     FusedPlan fp;
@@ -1545,8 +1661,12 @@ int cs_mrs_kwta_units_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval,
     int cus = 0;
     const int dst = device_cus(&cus);
     if (dst != CS_OK) return dst;
-    if (blocks_plan(geo, xt, aug, y, out, k, keep_sums, lists ? ocap : 0, lvec, cus, &bp, unit))
+    if (blocks_plan(geo, xt, aug, y, out, k, keep_sums, lists ? ocap : 0, lvec, cus, &bp, unit)) {
+      StreamPlan tp;
+      if (stream_plan(geo, xt, aug, y, out, k, keep_sums, cus, &tp, unit))
+        return launch_stream(tp, s, idx, lval, cnt, aug, bias, y, out, lo, geo);
       return launch_blocks(bp, s, idx, lval, cnt, aug, bias, y, out, lo, geo);
+    }
   }
   // two kernels: the sums into y, then k-WTA on the [rows * c_out / unit][unit]
   // view of y (dense output only)
@@ -1603,6 +1723,14 @@ int cs_mrs_plan(cs_dtype xt, int cap, int b, int h, int w, int c_in, int kh, int
     info[6] = bp.blocks;
     info[7] = (int64_t)bp.shmem;
     info[8] = bp.gb;
+    StreamPlan tp;                                        // the table streamed: its own kernel
+    if (stream_plan(geo, xt, nullptr, nullptr, nullptr, k, 1, 0, &tp)) {
+      info[2] = tp.sa.RB;
+      info[3] = tp.sa.nblocks;
+      info[6] = tp.blocks;
+      info[7] = (int64_t)tp.shmem;
+      info[8] = tp.gb;
+    }
     return CS_OK;
   }
   FusedPlan fp;

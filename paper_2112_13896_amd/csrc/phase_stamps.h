@@ -12,7 +12,7 @@
 // 2 conv1 products, 3 conv1 k-WTA, 4 conv1 lists out, 5 conv2 staged,
 // 6 conv2 products, 7 conv2 pool + k-WTA + lists, 8 linear1 staged,
 // 9 linear1 products, 10 linear1 sums, 11 linear1 threshold, 12 linear1
-// lists, 13 end (output layer), 15 count; the table-block kernel 16 tile
+// lists, 13 end (output layer), 15 count; the table-block kernels 16 tile
 // start, 17 products, 18 epilogue, 31 count, in its k-WTA on the lanes' own
 // columns 19 threshold search, 20 winner masks, and 21 the time of a tile
 // spent in the table blocks' products (measured per block with CS_CLOCK, added

@@ -66,7 +66,8 @@ __device__ __forceinline__ void dense_body(const int8_t* __restrict__ x,
                                            const DenseArgs& da, uint32_t blk) {
   static_assert(BD >= 512 && BD % 64 == 0, "the weight staging takes 512 threads");
   extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // a scalar: uniform loops
   const int Hp = geo.Ho / POOL, Wp = geo.Wo / POOL;
   const int C = geo.C, W = geo.W;
   const uint32_t img = fdiv(blk, da.fd_timg);

@@ -2463,10 +2463,16 @@ void launch_dense_chain(const cs::DenseArgs& da, const ScatterPlan& scp, const G
                         geo2,
                         sp.sa,
                         nx};
-  if constexpr (GA)
-    hipLaunchKernelGGL((cs::dense_gather_sample<POOL, KW, KM>), dim3((unsigned)geo0.B),
-                       dim3(cs::GATH_BD), shmem, s, a);
-  else
+  if constexpr (GA) {
+    // few images: even four launches in flight (the hardware queues) leave each
+    // image a compute unit of its own
+    if (geo0.B <= kPlanCus / 4)
+      hipLaunchKernelGGL((cs::dense_gather_sample<POOL, KW, KM, 4>), dim3((unsigned)geo0.B),
+                         dim3(cs::GATH_BD), shmem, s, a);
+    else
+      hipLaunchKernelGGL((cs::dense_gather_sample<POOL, KW, KM, 8>), dim3((unsigned)geo0.B),
+                         dim3(cs::GATH_BD), shmem, s, a);
+  } else
     hipLaunchKernelGGL((cs::dense_scatter_sample<POOL, KW, KM>), dim3((unsigned)geo0.B),
                        dim3(cs::SCAT_BD), shmem, s, a);
 }

@@ -68,7 +68,8 @@ __device__ __forceinline__ void gather_body(const uint16_t* __restrict__ lidx,
   constexpr int NPR = G / 2;                // set pairs
   constexpr int TAB_PAIR_B = T * GATH_C * 4;   // bytes of one pair's table
   extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // a scalar: uniform loops and branches
   const int H = geo.H, W = geo.W, P = geo.P, Wo = geo.Wo, n = geo.n, c_out = geo.c_out;
   const int npix = H * W;                                          // <= GATH_BD (host)
   const int64_t prow0 = (int64_t)blk * npix;

@@ -73,7 +73,8 @@ struct NextLayer {
 // the sum.  ws: SAMPLE_BD / 64 ints.  Barriers inside (call uniformly, with
 // every thread active).
 __device__ __forceinline__ int sample_scan(int v, int* ws, int* total) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int incl = (int)wave_incl_scan((uint32_t)v, 0u, OpAdd{});
   if (lane == 63) ws[wv] = incl;
   __syncthreads();
@@ -146,7 +147,8 @@ __device__ __forceinline__ void sample_body(const uint16_t* __restrict__ lidx,
                                             int32_t* __restrict__ dcnt = nullptr) {
   using E = typename Aug<T>::type;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = geo.n, G = geo.G, C = geo.C, c_out = geo.c_out, cap = geo.cap;
   const int npix = sa.npix, ne = npix * cap;
   A* acc = reinterpret_cast<A*>(smem);                              // [S][n][G]

@@ -618,3 +618,33 @@ def test_dense_chain3_matches_separate_calls(case):
         layers, x, [W1, W2, W3.reshape(c_out3, -1), W4.reshape(c_out4, -1)],
         [host(b1), host(b2), host(b3), host(b4)], [got[0], got[2], got[4], got[6]],
         [got[1], got[3], got[5], None])
+
+
+@pytest.mark.parametrize("b", [1, 64, 65])
+def test_dense_chain3_batch_rule(b):
+    """Up to 64 images cs_conv2d_dense_kwta_chain3 runs with the registers of
+    four wavefronts a SIMD, above with those of eight: the same bits as the
+    layers' own calls on both sides of the line."""
+    r = np.random.default_rng(b)
+    x = dev(r.integers(-127, 128, size=(b, 16, 16, 1)).astype(np.int8))
+    W1 = r.integers(1, 128, size=(64, 3, 3, 1)).astype(np.int8)
+    W2, W3, W4 = (weights(r, 64, 3, 3, 64, 16, "i8"), weights(r, 100, 4, 4, 64, 4, "i8"),
+                  weights(r, 12, 1, 1, 100, 1, "i8"))
+    b1, b2, b3, b4 = (dev(r.integers(-1000, 1001, size=m).astype(np.int32))
+                      for m in (64, 64, 100, 12))
+    a1, a2, a3, a4 = (ops.aug_to_device(ops.pack(Wx.reshape(Wx.shape[0], -1), nx)[0])
+                      for Wx, nx in ((W1, 1), (W2, 16), (W3, 4), (W4, 1)))
+    got = ops.conv2d_dense_kwta_chain3(
+        x, a1, 3, 3, 1, 1, 1, b1, 2, k=8, shift=8, aug2=a2, kh2=3, kw2=3, n2=16, pad2=1, bias2=b2,
+        pool2=2, k2=8, shift2=8, aug3=a3, n3=4, bias3=b3, k3=10, shift3=5, aug4=a4, n4=1,
+        bias4=b4, keep_sums=True)
+    y, lists = ops.conv2d_dense_kwta(x, a1, 3, 3, 1, 1, 1, b1, 2, k=8, out_dtype=torch.int8,
+                                     shift=8, keep_sums=True, cap=ops.list_capacity(8))
+    y2, lists2 = ops.mrs_kwta_conv2d(*lists, (b, 8, 8, 64), a2, 3, 3, 16, 1, 1, b2, 2, k=8,
+                                     out_dtype=torch.int8, shift=8, keep_sums=True,
+                                     cap=ops.list_capacity(8))
+    y3, _, y4 = ops.mrs_kwta_chain2(*lists2, (b, 4, 4, 64), a3, 4, 4, 4, 1, 0, b3, 1, k=10,
+                                    shift=5, aug2=a4, n2=1, bias2=b4, keep_sums=True)
+    torch.cuda.synchronize()
+    for i, e in ((0, y), (2, y2), (4, y3), (6, y4)):
+        assert np.array_equal(host(got[i]).reshape(-1), host(e).reshape(-1)), i

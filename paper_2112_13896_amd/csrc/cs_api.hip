@@ -723,7 +723,7 @@ int launch_blocks(const BlocksPlan& pl, hipStream_t stream, const uint16_t* idx,
 // ------------------------------------- fp32 layers, table streamed through LDS
 struct StreamPlan {
   cs::StreamArgs sa;
-  int gb, kp, threads;
+  int gb, kp, threads, slices;
   int64_t blocks;
   size_t shmem;
 };
@@ -738,22 +738,28 @@ bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
                  const void* out, int k, int write_sums, int cus, StreamPlan* pl, int unit = 0) {
   if (xt != CS_F32 || geo.pool != 1) return false;
   if (unit <= 0) unit = geo.c_out;
-  const int n = geo.n, G = geo.G;
-  const int log2n = ilog2_exact(n), log2G = ilog2_exact(G);
-  if (log2n < 0 || log2G < 2 || geo.c_out > 256) return false;
+  const int n = geo.n;
+  const int log2n = ilog2_exact(n);
+  // sets of a slice: all of them, or (sums of longer rows) those of 256 channels
+  const bool wide = geo.c_out > 256;
+  if (log2n < 0 || n > 16) return false;
+  if (wide && (k >= 0 || geo.KH * geo.KW != 1 || geo.c_out % 256 != 0)) return false;
+  const int G = wide ? 256 / n : geo.G;
+  const int log2G = ilog2_exact(G);
+  if (log2G < 2) return false;
   if (geo.cap % 4 != 0 || !aligned(aug, 16) || !aligned(y, 16) || !aligned(out, 16)) return false;
   const int T = geo.KH * geo.KW;
   const int64_t R = (int64_t)T * geo.C;
   const int64_t items = (int64_t)geo.B * geo.Ho * geo.Wo;
   const int64_t in_rows = (int64_t)geo.B * geo.H * geo.W;
-  if (items * geo.c_out >= INT32_MAX || in_rows * geo.cap >= INT32_MAX || R * G >= INT32_MAX)
+  if (items * geo.c_out >= INT32_MAX || in_rows * geo.cap >= INT32_MAX || R * geo.G >= INT32_MAX)
     return false;
   const int gb = G > 16 ? G / 16 : 1;
   const int kp = gb * n, U = G / gb;
   if (gb > 2 || (kp != 8 && kp != 16)) return false;
   const int64_t row_b = (int64_t)G * 8;
   // a table that stays in LDS next to a workgroup's accumulators: blocks_plan
-  if ((int64_t)2 * n * cs::BLK_BD * 4 + R * row_b <= (int64_t)(kCuLds / 2)) return false;
+  if (!wide && (int64_t)2 * n * cs::BLK_BD * 4 + R * row_b <= (int64_t)(kCuLds / 2)) return false;
   cs::StreamArgs& sa = pl->sa;
   const int max_rows = (int)(cs::STREAM_BLOCK / row_b);
   int64_t RB = 0;
@@ -776,13 +782,13 @@ bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
   sa.log2G = log2G;
   sa.k = k;
   sa.write_sums = write_sums;
-  const int log2Us = unit % kp == 0 ? ilog2_exact(unit / kp) : -1;
+  const int log2Us = wide ? sa.log2U : (unit % kp == 0 ? ilog2_exact(unit / kp) : -1);
   if (log2Us < 0 || log2Us > sa.log2U) return false;
   sa.log2Us = log2Us;
   const size_t tb = ((size_t)RB * row_b + cs::STREAM_PIECE - 1) / cs::STREAM_PIECE * cs::STREAM_PIECE;
   sa.off_t0 = (uint32_t)kp * cs::STREAM_BD * 4;
   sa.off_t1 = sa.off_t0 + (sa.nblocks > 1 ? (uint32_t)tb : 0u);
-  sa.table_bytes = R * row_b;
+  sa.row_stride = geo.G * 8;
   sa.fd_wo = cs::make_fastdiv((uint32_t)geo.Wo);
   sa.fd_ho = cs::make_fastdiv((uint32_t)geo.Ho);
   sa.fd_kw = cs::make_fastdiv((uint32_t)geo.KW);
@@ -790,8 +796,14 @@ bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
   // compute units, and in them the fewest wavefronts a workgroup (at least four,
   // which share the table's copies)
   const int ppw = 64 / U, units = cus > 0 ? cus : kPlanCus;
-  const int64_t rounds = (items + (int64_t)units * 16 * ppw - 1) / ((int64_t)units * 16 * ppw);
-  int64_t waves = (items + rounds * units * ppw - 1) / (rounds * units * ppw);
+  pl->slices = geo.G / G;
+  const int64_t px = items * pl->slices;
+  // Below, the table's trip through LDS takes longer than the few sums (1x1, n = 16:
+  // four images 7x7x512 -> 2048, 1,568 slices of pixels against 512 rows, 9.1 us, the
+  // table slices 8.1; eight images 10.0 against 18.9)
+  if (wide && px < 4 * R * gb) return false;
+  const int64_t rounds = (px + (int64_t)units * 16 * ppw - 1) / ((int64_t)units * 16 * ppw);
+  int64_t waves = (px + rounds * units * ppw - 1) / (rounds * units * ppw);
   waves = waves < 4 ? 4 : waves;
   sa.P = (int)waves * ppw;
   pl->threads = (int)waves * 64;
@@ -799,16 +811,17 @@ bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
   pl->gb = gb;
   pl->kp = kp;
   pl->shmem = (size_t)sa.off_t1 + tb;
-  return pl->shmem <= kCuLds && pl->blocks < INT32_MAX;
+  return pl->shmem <= kCuLds && pl->blocks < INT32_MAX && pl->slices <= 65535;
 }
 
 int launch_stream(const StreamPlan& pl, hipStream_t stream, const uint16_t* idx, const void* lval,
                   const int32_t* cnt, const void* aug, const void* bias, void* y, void* out,
                   const cs::ListOut& lo, const cs::ConvGeom& geo) {
 #define CS_STREAM(GB_, CH_, KP_)                                                             \
-  hipLaunchKernelGGL((cs::mrs_stream_f32<float, GB_, CH_, KP_>), dim3((unsigned)pl.blocks),   \
-                     dim3(pl.threads), pl.shmem, stream, idx, static_cast<const float*>(lval), \
-                     cnt, static_cast<const uint2*>(aug), static_cast<const float*>(bias),    \
+  hipLaunchKernelGGL((cs::mrs_stream_f32<float, GB_, CH_, KP_>),                              \
+                     dim3((unsigned)pl.blocks, (unsigned)pl.slices), dim3(pl.threads),        \
+                     pl.shmem, stream, idx, static_cast<const float*>(lval), cnt,             \
+                     static_cast<const uint2*>(aug), static_cast<const float*>(bias),         \
                      static_cast<float*>(y), static_cast<float*>(out), lo, geo, pl.sa)
 #define CS_STREAM_KP(GB_, CH_)              \
   do {                                      \
@@ -1234,9 +1247,16 @@ int mrs_launch_tiled(cs_dtype xt, const uint16_t* idx, const void* lval, const i
 // Sums of a layer: one workgroup per sample for a linear layer, else the fused
 // kernel (lists staged in LDS) when the layer suits it, else the table-slice
 // kernel, else the one-lane-per-output kernel.
+// wide: the sums of a 1x1 layer of more than 256 channels may take the streamed
+// table in slices of 256 (32 images: 7x7x512 -> 2048 31.1 -> 15.6 us, 28x28x128 -> 512
+// 140.7 -> 27.5).  Not the sums that a k-WTA of its own follows: they are added in
+// list order there, by parts in the table slices, and at near-ties the winners would
+// change.  Not several taps: added in order, so many products have a larger rounding
+// error than by parts (3x3x512: 9.2e-8 of the sums' rms against 7.1e-8; 1x1 the
+// other way, 4.2e-8 against 4.8e-8).
 int mrs_launch(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t* cnt,
                const cs::ConvGeom& geo, const void* aug, const void* bias, void* y,
-               hipStream_t stream) {
+               hipStream_t stream, bool wide = false) {
   SamplePlan sp;
   if (sample_plan(geo, xt, -1, 0, 1, &sp))
     return launch_sample(sp, xt, xt, stream, idx, lval, cnt, aug, bias, y, nullptr,
@@ -1262,6 +1282,10 @@ int mrs_launch(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t
       return launch_blocks(bp, stream, idx, lval, cnt, aug, bias, y, nullptr,
                            cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
     }
+    StreamPlan wp;
+    if (wide && geo.c_out > 256 && stream_plan(geo, xt, aug, y, nullptr, -1, 1, cus, &wp))
+      return launch_stream(wp, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                           cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
     FusedPlan fp;
     if (fused_plan(geo, xt, aug, y, -1, 0, 1, 0, 0, &fp))
       return launch_fused(fp, xt, xt, stream, idx, lval, cnt, aug, bias, y, nullptr,
@@ -1462,7 +1486,7 @@ int dense_launch(cs_dtype xt, const void* x, const cs::ConvGeom& geo, const void
   }
   const int r = compact_checked(xt, x, (int64_t)geo.B * geo.H * geo.W, geo.C, idx, lv, cnt, s);
   if (r != CS_OK) return r;
-  return mrs_launch(xt, idx, lv, cnt, geo, aug, bias, y, s);
+  return mrs_launch(xt, idx, lv, cnt, geo, aug, bias, y, s, true);
 }
 
 constexpr int kMaxDevices = 64;
@@ -1555,7 +1579,7 @@ int cs_mrs_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval, const int3
   if (cap < 1) return CS_ERR_SHAPE;
   if (!idx || !lval || !cnt || !aug || !y) return CS_ERR_ARG;
   geo.cap = cap;
-  return mrs_launch(xt, idx, lval, cnt, geo, aug, bias, y, static_cast<hipStream_t>(stream));
+  return mrs_launch(xt, idx, lval, cnt, geo, aug, bias, y, static_cast<hipStream_t>(stream), true);
 }
 
 int cs_mrs_kwta_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t* cnt,

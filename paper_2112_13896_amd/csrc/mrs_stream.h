@@ -26,6 +26,12 @@
 // 3x3/2, 13 images, 16 of 128 28.4 -> 20.8 us.  Of the 3x3 layer's time the vector
 // units are busy a little over half; reading a chunk's table entries a chunk
 // ahead, or four entries' accumulators together, changed nothing (36.0, 37.1 us).
+//
+// The sums alone of a 1x1 layer of more than 256 channels take the same kernel, 256
+// channels a workgroup (grid y): a pixel's list is walked once per slice, and the
+// slices' tables, which no compute unit could hold side by side, are streamed.
+// Against the table-slice kernel, 32 images: 7x7x512 -> 2048, 51 in 31.1 -> 15.6 us;
+// 14x14x256 -> 1024, 25 in 38.7 -> 19.8; 28x28x128 -> 512, 12 in 140.7 -> 27.5.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -53,12 +59,12 @@ struct StreamArgs {
   int nblocks;        // ceil(R / RB)
   int tpb;            // taps per block, or 0: a block is a channel range of one tap
   int cblocks;        // channel blocks per tap (C / RB) when tpb == 0
-  int log2n, log2G;
+  int log2n, log2G;   // kernels per set; sets of a slice
   int k;              // k-WTA winners per unit; -1: sums only
   int write_sums;
   int log2Us;         // lanes per k-WTA unit
   uint32_t off_t0, off_t1;   // LDS byte offsets of the table buffers
-  int64_t table_bytes;       // R * G * 8
+  int row_stride;            // bytes of a table row in memory, all G sets
   FastDiv fd_wo, fd_ho, fd_kw;
 };
 
@@ -142,14 +148,14 @@ __device__ __forceinline__ void stream_search(const uint32_t (&sl)[N], const uin
 // as one list (non-zero values, ascending index) or densely.
 template <typename TO, int KP, int BD>
 __device__ __forceinline__ void stream_kwta(const float* acc, int log2U, int log2Us,
-                                             int64_t row, bool live, int c_out, int k,
+                                             int64_t row, bool live, int c_out, int c0, int k,
                                              int write_sums, float* __restrict__ y,
                                              TO* __restrict__ out, const ListOut& lo) {
   const int tid = threadIdx.x;
   const int p = tid & ((1 << log2U) - 1);                // lane position in the group
   const int ps = p & ((1 << log2Us) - 1);                // lane position in its unit
   const int c_unit = KP << log2Us;                       // channels per k-WTA unit
-  const int o0 = p * KP;                                 // first channel of the lane
+  const int o0 = c0 + p * KP;                            // first channel of the lane
   constexpr uint32_t kAll = (1u << KP) - 1u;
   if (write_sums && live) {
     float* yr = y + row * c_out + o0;                    // 16-byte aligned (host)
@@ -397,6 +403,8 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = (int)blockDim.x >> 6;
   const int C = geo.C, T_ = geo.KH * geo.KW, R = T_ * C;
   const int u = tid & ((1 << sa.log2U) - 1);             // the lane's sets u*GB .. u*GB+GB-1
+  // sums of rows of more than 256 channels: a slice of the sets a workgroup
+  const int set0 = (int)blockIdx.y << sa.log2G, ch0 = set0 << sa.log2n;
   float* acc = reinterpret_cast<float*>(smem);           // [KP][STREAM_BD]
   const int log2row = sa.log2G + 3;                      // bytes of a table row
   const uint32_t lane_tab = (uint32_t)(u * GB * 8);
@@ -404,16 +412,16 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
 #pragma unroll
   for (int j = 0; j < GB; ++j) col[j] = (uint32_t)tid * 4u + ((uint32_t)(j << sa.log2n) << STREAM_SHIFT);
 
-  // rows [r0, r0 + RB) of the table (the last block's end) to LDS offset off,
-  // STREAM_PIECE bytes a wavefront and instruction; a lane past the table reads
-  // its last 16 bytes (the buffers are whole pieces)
+  // rows [r0, r0 + RB) of the slice's table (the last block's end) to LDS offset
+  // off, STREAM_PIECE bytes a wavefront and instruction; a lane past the table
+  // reads its last row (the buffers are whole pieces)
   auto copy_block = [&](int r0, uint32_t off) {
-    const int64_t b0 = (int64_t)r0 << log2row;
     const int rows = R - r0 < sa.RB ? R - r0 : sa.RB;
     const int bytes = rows << log2row;
     for (int p = wv; p * STREAM_PIECE < bytes; p += nwv) {           // uniform
-      int64_t g = b0 + p * STREAM_PIECE + 16 * (tid & 63);
-      g = g < sa.table_bytes - 16 ? g : sa.table_bytes - 16;
+      const int at = p * STREAM_PIECE + 16 * (tid & 63);
+      const int row = min(at >> log2row, rows - 1);
+      const int64_t g = (int64_t)(r0 + row) * sa.row_stride + set0 * 8 + (at & ((1 << log2row) - 1));
       __builtin_amdgcn_global_load_lds(
           reinterpret_cast<const __attribute__((address_space(1))) void*>(
               reinterpret_cast<uintptr_t>(aug) + (uintptr_t)g),
@@ -452,7 +460,7 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
   for (int j = 0; j < KP; ++j) bv[j] = 0.f;
   if (bias != nullptr) {                                 // uniform
 #pragma unroll
-    for (int j = 0; j < KP; ++j) bv[j] = bias[u * KP + j];
+    for (int j = 0; j < KP; ++j) bv[j] = bias[ch0 + u * KP + j];
   }
   StreamPre q;
   stream_prefetch(q, lidx, lval, lcnt, geo, place, 0, 0, sa.fd_kw);
@@ -496,8 +504,8 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
   }
   CS_STAMP(17);
   CS_STAMP_ADD(21, blk_time);
-  stream_kwta<TO, KP, STREAM_BD>(acc, sa.log2U, sa.log2Us, (int64_t)item, live, geo.c_out, sa.k,
-                                 sa.write_sums, y, out, lo);
+  stream_kwta<TO, KP, STREAM_BD>(acc, sa.log2U, sa.log2Us, (int64_t)item, live, geo.c_out, ch0,
+                                 sa.k, sa.write_sums, y, out, lo);
   CS_STAMP(18);
 }
 

@@ -228,12 +228,16 @@ int cs_mrs_kwta_units_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval,
  *          rows of more than 128 or k > 32; 6 fp32 layer without pooling,
  *          sets and kernels per set powers of two, n <= 16, c_out <= 256:
  *          tiles complete in the channel dimension with the packed table
- *          streamed through LDS in blocks of rows, k-WTA in the epilogue);
+ *          streamed through LDS in blocks of rows, k-WTA in the epilogue; and
+ *          the sums alone (k = -1) of such a 1x1 layer of a multiple of 256
+ *          channels above 256, in slices of 256);
  *          for path 6: [1] k-WTA selection (1-3 four lanes per row with
  *          top-8/16/32 lists, 4 sixteen lanes per row, 5 the lanes that
  *          summed a pixel, on their own accumulators, bit by bit, 6-8 the
- *          same four lanes with top-8/16/32 lists), [2] table rows per
- *          block, [3] blocks, [6]
+ *          same four lanes with top-8/16/32 lists; 9 the kernel that streams
+ *          the table, whose lanes select as in 5), [2] table rows per
+ *          block, [3] blocks, with [1] = 9 [4] channel slices and [5] log2 of
+ *          the parts a pixel's list is added in (of the slices), [6]
  *          workgroups, [7] LDS bytes, [8] sets per lane; for paths 3 and
  *          5: [6] workgroups, [7] LDS bytes per workgroup, [8] entry slices
  *          per packed set; for path 4: [2] output rows per band, [6]

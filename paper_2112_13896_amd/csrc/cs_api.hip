@@ -728,21 +728,30 @@ struct StreamPlan {
   size_t shmem;
 };
 
+// How the kernel that a layer of more than 256 channels runs on otherwise adds a
+// pixel's sums: in 1 << log2S parts, in order from zero or in pairs.
+struct SumParts {
+  int log2S;
+  bool pairs;
+};
+
 // The layers that blocks_plan takes whose table does not stay in LDS, when a
 // pixel's channels divide into 4, 8 or 16 lanes of 8 or 16 channels: measured
 // faster than the table-block kernel at every such layer tried (14x14x256 3x3,
 // 64 images, 41.7 -> 36.2 us; 1x1 1024 -> 256 33.0 -> 27.1 us; 56x56x128 3x3/2, 13
 // images, 28.4 -> 20.8 us).  cus: compute units of the device, or 0 when only
 // planning.  unit: as blocks_plan.
+// parts: the sums alone of a 1x1 layer of more than 256 channels, in slices of 256.
 bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const void* y,
-                 const void* out, int k, int write_sums, int cus, StreamPlan* pl, int unit = 0) {
+                 const void* out, int k, int write_sums, int cus, StreamPlan* pl, int unit = 0,
+                 const SumParts* parts = nullptr) {
   if (xt != CS_F32 || geo.pool != 1) return false;
   if (unit <= 0) unit = geo.c_out;
   const int n = geo.n;
   const int log2n = ilog2_exact(n);
   // sets of a slice: all of them, or (sums of longer rows) those of 256 channels
-  const bool wide = geo.c_out > 256;
-  if (log2n < 0 || n > 16) return false;
+  const bool wide = parts != nullptr;
+  if (log2n < 0 || n > 16 || wide != (geo.c_out > 256)) return false;
   if (wide && (k >= 0 || geo.KH * geo.KW != 1 || geo.c_out % 256 != 0)) return false;
   const int G = wide ? 256 / n : geo.G;
   const int log2G = ilog2_exact(G);
@@ -756,7 +765,7 @@ bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
     return false;
   const int gb = G > 16 ? G / 16 : 1;
   const int kp = gb * n, U = G / gb;
-  if (gb > 2 || (kp != 8 && kp != 16)) return false;
+  if (gb > 2 || (kp != 8 && kp != 16) || (wide && U != 16)) return false;
   const int64_t row_b = (int64_t)G * 8;
   // a table that stays in LDS next to a workgroup's accumulators: blocks_plan
   if (!wide && (int64_t)2 * n * cs::BLK_BD * 4 + R * row_b <= (int64_t)(kCuLds / 2)) return false;
@@ -769,6 +778,11 @@ bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
     sa.tpb = std::min(max_rows / geo.C, T);
     RB = (int64_t)sa.tpb * geo.C;
   } else {
+    // (wide, larger tables: every part of a list, short as it is, would wait for the
+    // table's blocks: 32 images 7x7x512 -> 2048 in four parts 32.5 against the table
+    // slices' 31.7 us, 14x14x1024 -> 2048, stride 2, 49.4 against 38.7.  Tables of one
+    // block took 0.35 to 1.02 times the other kernel's time from 1 to 64 images.)
+    if (wide) return false;
     RB = max_rows;
     while (RB >= 4 && geo.C % RB != 0) --RB;
     if (RB < 4) return false;
@@ -794,18 +808,17 @@ bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
   sa.fd_kw = cs::make_fastdiv((uint32_t)geo.KW);
   // one workgroup per compute unit at a time: the fewest rounds over the
   // compute units, and in them the fewest wavefronts a workgroup (at least four,
-  // which share the table's copies)
+  // which share the table's copies, and whole pixels)
+  sa.log2S = wide ? parts->log2S : 0;
+  sa.pairs = wide && parts->pairs ? 1 : 0;
   const int ppw = 64 / U, units = cus > 0 ? cus : kPlanCus;
   pl->slices = geo.G / G;
-  const int64_t px = items * pl->slices;
-  // Below, the table's trip through LDS takes longer than the few sums (1x1, n = 16:
-  // four images 7x7x512 -> 2048, 1,568 slices of pixels against 512 rows, 9.1 us, the
-  // table slices 8.1; eight images 10.0 against 18.9)
-  if (wide && px < 4 * R * gb) return false;
+  const int64_t px = items * pl->slices << sa.log2S;      // groups of U lanes
   const int64_t rounds = (px + (int64_t)units * 16 * ppw - 1) / ((int64_t)units * 16 * ppw);
   int64_t waves = (px + rounds * units * ppw - 1) / (rounds * units * ppw);
   waves = waves < 4 ? 4 : waves;
-  sa.P = (int)waves * ppw;
+  if ((ppw >> sa.log2S) < 1) return false;                 // a pixel's parts: one wavefront
+  sa.P = (int)waves * ppw >> sa.log2S;
   pl->threads = (int)waves * 64;
   pl->blocks = (items + sa.P - 1) / sa.P;
   pl->gb = gb;
@@ -817,19 +830,22 @@ bool stream_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
 int launch_stream(const StreamPlan& pl, hipStream_t stream, const uint16_t* idx, const void* lval,
                   const int32_t* cnt, const void* aug, const void* bias, void* y, void* out,
                   const cs::ListOut& lo, const cs::ConvGeom& geo) {
-#define CS_STREAM(GB_, CH_, KP_)                                                             \
-  hipLaunchKernelGGL((cs::mrs_stream_f32<float, GB_, CH_, KP_>),                              \
+#define CS_STREAM(GB_, CH_, KP_, WIDE_)                                                      \
+  hipLaunchKernelGGL((cs::mrs_stream_f32<float, GB_, CH_, KP_, WIDE_>),                       \
                      dim3((unsigned)pl.blocks, (unsigned)pl.slices), dim3(pl.threads),        \
                      pl.shmem, stream, idx, static_cast<const float*>(lval), cnt,             \
                      static_cast<const uint2*>(aug), static_cast<const float*>(bias),         \
                      static_cast<float*>(y), static_cast<float*>(out), lo, geo, pl.sa)
-#define CS_STREAM_KP(GB_, CH_)              \
-  do {                                      \
-    if (pl.kp == 8) CS_STREAM(GB_, CH_, 8); \
-    else CS_STREAM(GB_, CH_, 16);           \
+#define CS_STREAM_KP(GB_, CH_)                            \
+  do {                                                    \
+    if (pl.kp == 8) CS_STREAM(GB_, CH_, 8, false);        \
+    else CS_STREAM(GB_, CH_, 16, false);                  \
   } while (0)
   const bool ch = pl.sa.tpb == 0;
-  if (pl.gb == 1) {
+  if (geo.c_out > 256) {                                  // one block
+    if (pl.gb == 1) CS_STREAM(1, false, 16, true);
+    else CS_STREAM(2, false, 16, true);
+  } else if (pl.gb == 1) {
     if (ch) CS_STREAM_KP(1, true); else CS_STREAM_KP(1, false);
   } else {
     if (ch) CS_STREAM_KP(2, true); else CS_STREAM_KP(2, false);
@@ -1240,63 +1256,17 @@ int launch_rows(const RowsPlan& pl, cs_dtype ot, hipStream_t s, const uint16_t* 
   return launch_status();
 }
 
-int mrs_launch_tiled(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t* cnt,
-                     const cs::ConvGeom& geo, const void* aug, const void* bias, void* y,
-                     hipStream_t stream);
+struct TiledPlan {
+  cs::TiledArgs ta;
+  int gb;
+  size_t shmem;
+  dim3 grid;
+};
 
-// Sums of a layer: one workgroup per sample for a linear layer, else the fused
-// kernel (lists staged in LDS) when the layer suits it, else the table-slice
-// kernel, else the one-lane-per-output kernel.
-// wide: the sums of a 1x1 layer of more than 256 channels may take the streamed
-// table in slices of 256 (32 images: 7x7x512 -> 2048 31.1 -> 15.6 us, 28x28x128 -> 512
-// 140.7 -> 27.5).  Not the sums that a k-WTA of its own follows: they are added in
-// list order there, by parts in the table slices, and at near-ties the winners would
-// change.  Not several taps: added in order, so many products have a larger rounding
-// error than by parts (3x3x512: 9.2e-8 of the sums' rms against 7.1e-8; 1x1 the
-// other way, 4.2e-8 against 4.8e-8).
-int mrs_launch(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t* cnt,
-               const cs::ConvGeom& geo, const void* aug, const void* bias, void* y,
-               hipStream_t stream, bool wide = false) {
-  SamplePlan sp;
-  if (sample_plan(geo, xt, -1, 0, 1, &sp))
-    return launch_sample(sp, xt, xt, stream, idx, lval, cnt, aug, bias, y, nullptr,
-                         cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
-  ScatterPlan scp;
-  if (scatter_plan(geo, xt, aug, -1, 0, 1, &scp))
-    return launch_scatter(scp, CS_I32, stream, idx, lval, cnt, aug, bias, y, nullptr,
-                          cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
-  RowsPlan rp;
-  if (rows_plan(geo, xt, aug, -1, 0, 1, &rp))
-    return launch_rows(rp, CS_I32, stream, idx, lval, cnt, aug, bias, y, nullptr,
-                       cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
-  if (lists_vectorisable(xt, idx, lval, geo.cap)) {
-    BlocksPlan bp;
-    int cus = 0;
-    const int dst = device_cus(&cus);
-    if (dst != CS_OK) return dst;
-    if (blocks_plan(geo, xt, aug, y, nullptr, -1, 1, 0, false, cus, &bp)) {
-      StreamPlan tp;
-      if (stream_plan(geo, xt, aug, y, nullptr, -1, 1, cus, &tp))
-        return launch_stream(tp, stream, idx, lval, cnt, aug, bias, y, nullptr,
-                             cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
-      return launch_blocks(bp, stream, idx, lval, cnt, aug, bias, y, nullptr,
-                           cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
-    }
-    StreamPlan wp;
-    if (wide && geo.c_out > 256 && stream_plan(geo, xt, aug, y, nullptr, -1, 1, cus, &wp))
-      return launch_stream(wp, stream, idx, lval, cnt, aug, bias, y, nullptr,
-                           cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
-    FusedPlan fp;
-    if (fused_plan(geo, xt, aug, y, -1, 0, 1, 0, 0, &fp))
-      return launch_fused(fp, xt, xt, stream, idx, lval, cnt, aug, bias, y, nullptr,
-                          cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
-  }
-  return mrs_launch_tiled(xt, idx, lval, cnt, geo, aug, bias, y, stream);
-}
-
-int mrs_launch_tiled(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t* cnt,
-                     const cs::ConvGeom& geo, const void* aug, const void* bias, void* y,
-                     hipStream_t stream) {
+// The table-slice kernel's plan, or false when a slice of the table does not fit
+// the LDS or the sizes pass its 32-bit offsets (lists that are not vectorisable are
+// the caller's to check).
+bool tiled_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, int cus, TiledPlan* pl) {
   const bool one = geo.n == 1;
   const int nacc = one ? 1 : geo.n;
   const int T = geo.KH * geo.KW;
@@ -1309,7 +1279,7 @@ int mrs_launch_tiled(cs_dtype xt, const uint16_t* idx, const void* lval, const i
     gb = 1;
     Gs = table_slice(geo, esz, nacc, 1);
   }
-  cs::TiledArgs ta;
+  cs::TiledArgs& ta = pl->ta;
   ta.chunk_mode = T == 1 ? 1 : 0;
   ta.log2Q = geo.pool == 2 ? 2 : 0;
   // tap mode: each lane walks at most MRS_TAPS taps
@@ -1321,11 +1291,7 @@ int mrs_launch_tiled(cs_dtype xt, const uint16_t* idx, const void* lval, const i
   // 32-bit offsets inside the kernel: element offsets and lane counts below 2^31
   const bool fits32 = in_rows * geo.cap < INT32_MAX && items * geo.c_out < INT32_MAX &&
                       R * geo.G < INT32_MAX && items * geo.G * 64 < INT32_MAX;
-  if (!lists_vectorisable(xt, idx, lval, geo.cap) || Gs < 1 || log2S + ta.log2Q > 6 || !fits32)
-    return mrs_launch_simple(xt, idx, lval, cnt, geo, aug, bias, y, stream);
-  int cus = 0;
-  const int st = device_cus(&cus);
-  if (st != CS_OK) return st;
+  if (Gs < 1 || log2S + ta.log2Q > 6 || !fits32) return false;
   ta.Gs = Gs;
   ta.gslices = geo.G / Gs;
   ta.items = (int)items;
@@ -1355,14 +1321,93 @@ int mrs_launch_tiled(cs_dtype xt, const uint16_t* idx, const void* lval, const i
   const int64_t cap_blocks = ((int64_t)cus * bpc + ta.gslices - 1) / ta.gslices;
   if (blocks_per_slice > cap_blocks) blocks_per_slice = cap_blocks;
   if (blocks_per_slice < 1) blocks_per_slice = 1;
-  const dim3 grid((unsigned)(blocks_per_slice * ta.gslices));
+  pl->grid = dim3((unsigned)(blocks_per_slice * ta.gslices));
+  pl->gb = gb;
+  pl->shmem = shmem;
+  return true;
+}
+
+int mrs_launch_tiled(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t* cnt,
+                     const cs::ConvGeom& geo, const void* aug, const void* bias, void* y,
+                     hipStream_t stream) {
+  int cus = 0;
+  const int st = device_cus(&cus);
+  if (st != CS_OK) return st;
+  TiledPlan pl;
+  if (!lists_vectorisable(xt, idx, lval, geo.cap) || !tiled_plan(geo, xt, aug, cus, &pl))
+    return mrs_launch_simple(xt, idx, lval, cnt, geo, aug, bias, y, stream);
+  const bool one = geo.n == 1;
   if (xt == CS_I8)
-    launch_tiled_any<int8_t, int32_t>(one, gb, grid, shmem, stream, idx, lval, cnt, aug, bias,
-                                      y, geo, ta);
+    launch_tiled_any<int8_t, int32_t>(one, pl.gb, pl.grid, pl.shmem, stream, idx, lval, cnt, aug,
+                                      bias, y, geo, pl.ta);
   else
-    launch_tiled_any<float, float>(one, gb, grid, shmem, stream, idx, lval, cnt, aug, bias, y,
-                                   geo, ta);
+    launch_tiled_any<float, float>(one, pl.gb, pl.grid, pl.shmem, stream, idx, lval, cnt, aug,
+                                   bias, y, geo, pl.ta);
   return launch_status();
+}
+
+// The sums of a 1x1 layer of more than 256 channels on the streamed table, added as the
+// kernel they run on otherwise adds them: fp, the fused kernel's plan (NULL: the
+// table-slice kernel).  cus: as stream_plan.
+bool wide_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const void* y,
+               const FusedPlan* fp, int cus, StreamPlan* pl) {
+  if (xt != CS_F32 || geo.c_out <= 256 || geo.KH * geo.KW != 1) return false;
+  SumParts parts{0, true};
+  if (fp != nullptr) {
+    parts.log2S = fp->fa.log2S;
+  } else {
+    TiledPlan tp;
+    if (!tiled_plan(geo, xt, aug, cus > 0 ? cus : kPlanCus, &tp)) return false;
+    parts = SumParts{tp.ta.log2S, false};
+  }
+  return stream_plan(geo, xt, aug, y, nullptr, -1, 1, cus, pl, 0, &parts);
+}
+
+// Sums of a layer: one workgroup per sample for a linear layer, else the fused
+// kernel (lists staged in LDS) when the layer suits it, else the table-slice
+// kernel, else the one-lane-per-output kernel.
+// wide: fp32 sums of a 1x1 layer of more than 256 channels may take the streamed
+// table in slices of 256, added in the parts of the kernel they would run on
+// otherwise: the same bits.  The sums that a k-WTA kernel follows stay on that kernel.
+int mrs_launch(cs_dtype xt, const uint16_t* idx, const void* lval, const int32_t* cnt,
+               const cs::ConvGeom& geo, const void* aug, const void* bias, void* y,
+               hipStream_t stream, bool wide = false) {
+  SamplePlan sp;
+  if (sample_plan(geo, xt, -1, 0, 1, &sp))
+    return launch_sample(sp, xt, xt, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                         cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
+  ScatterPlan scp;
+  if (scatter_plan(geo, xt, aug, -1, 0, 1, &scp))
+    return launch_scatter(scp, CS_I32, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                          cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
+  RowsPlan rp;
+  if (rows_plan(geo, xt, aug, -1, 0, 1, &rp))
+    return launch_rows(rp, CS_I32, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                       cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
+  if (lists_vectorisable(xt, idx, lval, geo.cap)) {
+    BlocksPlan bp;
+    int cus = 0;
+    const int dst = device_cus(&cus);
+    if (dst != CS_OK) return dst;
+    if (blocks_plan(geo, xt, aug, y, nullptr, -1, 1, 0, false, cus, &bp)) {
+      StreamPlan tp;
+      if (stream_plan(geo, xt, aug, y, nullptr, -1, 1, cus, &tp))
+        return launch_stream(tp, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                             cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
+      return launch_blocks(bp, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                           cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
+    }
+    FusedPlan fp;
+    const bool fused = fused_plan(geo, xt, aug, y, -1, 0, 1, 0, 0, &fp);
+    StreamPlan wp;
+    if (wide && wide_plan(geo, xt, aug, y, fused ? &fp : nullptr, cus, &wp))
+      return launch_stream(wp, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                           cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
+    if (fused)
+      return launch_fused(fp, xt, xt, stream, idx, lval, cnt, aug, bias, y, nullptr,
+                          cs::ListOut{nullptr, nullptr, nullptr, 0}, geo);
+  }
+  return mrs_launch_tiled(xt, idx, lval, cnt, geo, aug, bias, y, stream);
 }
 
 // ------------------------------------- dense input, block CS, matrix cores
@@ -1702,6 +1747,17 @@ int cs_mrs_kwta_units_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval,
                        cs::ListOut{nullptr, nullptr, nullptr, 0});
 }
 
+static void report_stream(const StreamPlan& pl, int64_t* info) {
+  info[1] = 9;
+  info[2] = pl.sa.RB;
+  info[3] = pl.sa.nblocks;
+  info[4] = pl.slices;
+  info[5] = pl.sa.log2S;
+  info[6] = pl.blocks * pl.slices;
+  info[7] = (int64_t)pl.shmem;
+  info[8] = pl.gb;
+}
+
 int cs_mrs_plan(cs_dtype xt, int cap, int b, int h, int w, int c_in, int kh, int kw, int stride,
                 int pad, int c_out, int n, int pool, int k, int64_t* info) {
   if (!is_act_dtype(xt)) return CS_ERR_DTYPE;
@@ -1748,13 +1804,7 @@ int cs_mrs_plan(cs_dtype xt, int cap, int b, int h, int w, int c_in, int kh, int
     info[7] = (int64_t)bp.shmem;
     info[8] = bp.gb;
     StreamPlan tp;                                        // the table streamed: its own kernel
-    if (stream_plan(geo, xt, nullptr, nullptr, nullptr, k, 1, 0, &tp)) {
-      info[2] = tp.sa.RB;
-      info[3] = tp.sa.nblocks;
-      info[6] = tp.blocks;
-      info[7] = (int64_t)tp.shmem;
-      info[8] = tp.gb;
-    }
+    if (stream_plan(geo, xt, nullptr, nullptr, nullptr, k, 1, 0, &tp)) report_stream(tp, info);
     return CS_OK;
   }
   FusedPlan fp;
@@ -1767,6 +1817,12 @@ int cs_mrs_plan(cs_dtype xt, int cap, int b, int h, int w, int c_in, int kh, int
     info[10] = 1;
   } else if (k >= 0 && !fused) {
     info[10] = 1;
+  }
+  StreamPlan wp;
+  if (k < 0 && cap % 4 == 0 && wide_plan(geo, xt, nullptr, nullptr, fused ? &fp : nullptr, 0, &wp)) {
+    info[0] = 6;
+    report_stream(wp, info);
+    return CS_OK;
   }
   if (fused) {
     info[0] = 2;

@@ -27,11 +27,17 @@
 // units are busy a little over half; reading a chunk's table entries a chunk
 // ahead, or four entries' accumulators together, changed nothing (36.0, 37.1 us).
 //
-// The sums alone of a 1x1 layer of more than 256 channels take the same kernel, 256
-// channels a workgroup (grid y): a pixel's list is walked once per slice, and the
-// slices' tables, which no compute unit could hold side by side, are streamed.
-// Against the table-slice kernel, 32 images: 7x7x512 -> 2048, 51 in 31.1 -> 15.6 us;
-// 14x14x256 -> 1024, 25 in 38.7 -> 19.8; 28x28x128 -> 512, 12 in 140.7 -> 27.5.
+// The sums alone of a 1x1 layer of more than 256 channels whose table fits a block in
+// slices of 256 channels take the same kernel (WIDE), a slice a workgroup (grid y).  The
+// sums are added as the table-slice or fused kernel, which such a layer runs on
+// otherwise, adds them: in S parts, part s taking the list's chunks of four entries
+// s, s + S, ... from zero, the parts added in order (or in pairs), then the bias.  A
+// part is one group of U lanes on a list of its own - the entry at place 4 k + e of
+// part s is the pixel's entry 4 (s + S k) + e - so both kernels give the same bits.
+// Against those kernels, 32 images: 28x28x128 -> 512, 12 in, 138.4 -> 52.4 us (four
+// parts); 14x14x256 -> 1024, 25 in, 38.4 -> 20.9 (two); 14x14x64 -> 512, 25 in, 44.1 ->
+// 18.2 (four).  In list order the three took 25.4, 18.9 and 10.7: a part is a few
+// entries, and each group of lanes pays for its pixel's start and end.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -64,7 +70,9 @@ struct StreamArgs {
   int write_sums;
   int log2Us;         // lanes per k-WTA unit
   uint32_t off_t0, off_t1;   // LDS byte offsets of the table buffers
-  int row_stride;            // bytes of a table row in memory, all G sets
+  int row_stride;     // WIDE: bytes of a table row in memory, all G sets
+  int log2S;          // WIDE: parts of a pixel's list, at most 4; P = threads / (U S)
+  int pairs;          // WIDE: the parts are added in pairs, not in order
   FastDiv fd_wo, fd_ho, fd_kw;
 };
 
@@ -148,14 +156,14 @@ __device__ __forceinline__ void stream_search(const uint32_t (&sl)[N], const uin
 // as one list (non-zero values, ascending index) or densely.
 template <typename TO, int KP, int BD>
 __device__ __forceinline__ void stream_kwta(const float* acc, int log2U, int log2Us,
-                                             int64_t row, bool live, int c_out, int c0, int k,
+                                             int64_t row, bool live, int c_out, int k,
                                              int write_sums, float* __restrict__ y,
                                              TO* __restrict__ out, const ListOut& lo) {
   const int tid = threadIdx.x;
   const int p = tid & ((1 << log2U) - 1);                // lane position in the group
   const int ps = p & ((1 << log2Us) - 1);                // lane position in its unit
   const int c_unit = KP << log2Us;                       // channels per k-WTA unit
-  const int o0 = c0 + p * KP;                            // first channel of the lane
+  const int o0 = p * KP;                                 // first channel of the lane
   constexpr uint32_t kAll = (1u << KP) - 1u;
   if (write_sums && live) {
     float* yr = y + row * c_out + o0;                    // 16-byte aligned (host)
@@ -246,6 +254,17 @@ struct TapPlace {
   uint32_t off;            // its list row's first entry, q * cap (modulo 2^32)
 };
 
+// The part of a pixel's list that a group of lanes takes (the whole list: 0, 0).
+struct ListPart {
+  int log2S;               // parts
+  int s4;                  // 4 * this part
+  // entries of this part among the first m of the list
+  __device__ __forceinline__ int count(int m) const {
+    const int rounds = m >> (log2S + 2), rest = m - (rounds << (log2S + 2));
+    return 4 * rounds + max(0, min(rest - s4, 4));
+  }
+};
+
 // A tap's list, its first STREAM_PRE groups of sixteen entries already loaded:
 // lane p of a quad holds entries g0 + 16 i + 4p .. + 3 in ch[i].
 struct StreamPre {
@@ -256,8 +275,9 @@ struct StreamPre {
 
 __device__ __forceinline__ void stream_load(BChunk& c, const uint16_t* __restrict__ lidx,
                                             const float* __restrict__ lval, uint32_t base, int pos,
-                                            int cap) {
-  const size_t e = (size_t)(base + (uint32_t)min(pos, cap - 4));      // inside the row
+                                            int cap, ListPart part) {
+  // pos a multiple of four; inside the row
+  const size_t e = (size_t)(base + (uint32_t)min((pos << part.log2S) + part.s4, cap - 4));
   c.idx = *reinterpret_cast<const uint2*>(lidx + e);
   c.val = *reinterpret_cast<const float4*>(lval + e);
 }
@@ -266,7 +286,7 @@ __device__ __forceinline__ void stream_prefetch(StreamPre& tp, const uint16_t* _
                                                 const float* __restrict__ lval,
                                                 const int32_t* __restrict__ lcnt,
                                                 const ConvGeom& geo, const TapPlace& pl, int t,
-                                                int j0, const FastDiv& fd_kw) {
+                                                int j0, const FastDiv& fd_kw, ListPart part) {
   const int ky = (int)fdiv((uint32_t)t, fd_kw), kx = t - ky * geo.KW;         // uniform
   const bool in = t < geo.KH * geo.KW;
   const uint32_t dq = in ? (uint32_t)(ky * geo.W + kx) : 0u;
@@ -279,7 +299,8 @@ __device__ __forceinline__ void stream_prefetch(StreamPre& tp, const uint16_t* _
   const int p = (j0 & ~3) + 4 * (int)(threadIdx.x & 3);
 #pragma unroll
   for (int i = 0; i < STREAM_PRE; ++i)
-    if (16 * i < geo.cap) stream_load(tp.ch[i], lidx, lval, base, p + 16 * i, geo.cap);   // uniform
+    if (16 * i < geo.cap)                                                     // uniform
+      stream_load(tp.ch[i], lidx, lval, base, p + 16 * i, geo.cap, part);
 }
 
 // Route + Sum of four entries into the lane's GB accumulators, in pairs as
@@ -328,9 +349,9 @@ __device__ __forceinline__ int stream_tap(const StreamPre& tp, const uint16_t* _
                                           const float* __restrict__ lval, int cap, int j0, int c_hi,
                                           int row_add, const unsigned char* smem, uint32_t tab,
                                           int log2row, uint32_t lane_tab,
-                                          const uint32_t (&col)[GB]) {
+                                          const uint32_t (&col)[GB], ListPart part) {
   if (tp.off < 0) return j0;
-  const int m = min(tp.cnt, cap);
+  const int m = part.count(min(tp.cnt, cap));
   const uint32_t row0 = tab + ((uint32_t)row_add << log2row);
   int end = m;
   // sixteen entries from list position g0 on; true: the list goes on after them
@@ -386,13 +407,53 @@ __device__ __forceinline__ int stream_tap(const StreamPre& tp, const uint16_t* _
   }
   while (true) {
     BChunk c;
-    stream_load(c, lidx, lval, (uint32_t)tp.off, g0 + 4 * (int)(threadIdx.x & 3), cap);
+    stream_load(c, lidx, lval, (uint32_t)tp.off, g0 + 4 * (int)(threadIdx.x & 3), cap, part);
     if (!group(c, g0)) return CH ? end : m;
     g0 += 16;
   }
 }
 
-template <typename TO, int GB, bool CH, int KP>
+// The sums of a pixel's 256 channels of a slice from its S parts' accumulators, and the
+// bias: of the sixteen channels of the S lanes' columns each lane finishes 16 / S, from
+// s * 16 / S on (s: its part; bv: their bias, yr: their place).  The groups of lanes read
+// different parts at a time - the same part of different rows would be one bank - and
+// turn the values back into part order in registers.
+template <int KP>
+__device__ __forceinline__ void stream_sum_parts(const float* acc, int log2S, int pairs, int s,
+                                                 const float (&bv)[KP], float* __restrict__ yr) {
+  static_assert(KP == 16, "sixteen lanes of sixteen channels a pixel");
+  const int tid = threadIdx.x, per = 16 >> log2S;
+  const float* col = acc + (tid & ~((16 << log2S) - 1)) + (tid & 15);   // part 0's column
+#pragma unroll
+  for (int j0 = 0; j0 < KP; j0 += 4) {
+    if (j0 >= per) break;                                // uniform
+    float v[4];
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const float* cj = col + (s * per + j0 + jj) * STREAM_BD;
+      float a = 0.f;
+      if (log2S == 0) {
+        a += cj[0];
+      } else if (log2S == 1) {
+        const float r0 = cj[16 * s], r1 = cj[16 * (1 - s)];
+        a = (a + (s ? r1 : r0)) + (s ? r0 : r1);
+      } else {
+        float r[4], q[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r[t] = cj[16 * ((t + s) & 3)];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) q[t] = (s & 1) ? r[(t + 3) & 3] : r[t];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r[t] = (s & 2) ? q[(t + 2) & 3] : q[t];
+        a = pairs ? (r[0] + r[1]) + (r[2] + r[3]) : (((a + r[0]) + r[1]) + r[2]) + r[3];
+      }
+      v[jj] = a + bv[j0 + jj];
+    }
+    *reinterpret_cast<float4*>(yr + j0) = make_float4(v[0], v[1], v[2], v[3]);
+  }
+}
+
+template <typename TO, int GB, bool CH, int KP, bool WIDE>
 __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
     const uint16_t* __restrict__ lidx, const float* __restrict__ lval,
     const int32_t* __restrict__ lcnt, const uint2* __restrict__ aug,
@@ -403,8 +464,11 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = (int)blockDim.x >> 6;
   const int C = geo.C, T_ = geo.KH * geo.KW, R = T_ * C;
   const int u = tid & ((1 << sa.log2U) - 1);             // the lane's sets u*GB .. u*GB+GB-1
-  // sums of rows of more than 256 channels: a slice of the sets a workgroup
-  const int set0 = (int)blockIdx.y << sa.log2G, ch0 = set0 << sa.log2n;
+  // sums of rows of more than 256 channels: a slice of the sets a workgroup, and a
+  // part of its pixel's list a group of U lanes
+  const int set0 = WIDE ? (int)blockIdx.y << sa.log2G : 0, ch0 = set0 << sa.log2n;
+  const int log2S = WIDE ? sa.log2S : 0;
+  const ListPart part{log2S, WIDE ? 4 * ((tid >> sa.log2U) & ((1 << log2S) - 1)) : 0};
   float* acc = reinterpret_cast<float*>(smem);           // [KP][STREAM_BD]
   const int log2row = sa.log2G + 3;                      // bytes of a table row
   const uint32_t lane_tab = (uint32_t)(u * GB * 8);
@@ -421,7 +485,9 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
     for (int p = wv; p * STREAM_PIECE < bytes; p += nwv) {           // uniform
       const int at = p * STREAM_PIECE + 16 * (tid & 63);
       const int row = min(at >> log2row, rows - 1);
-      const int64_t g = (int64_t)(r0 + row) * sa.row_stride + set0 * 8 + (at & ((1 << log2row) - 1));
+      const int64_t g = WIDE ? (int64_t)(r0 + row) * sa.row_stride + set0 * 8 +
+                                   (at & ((1 << log2row) - 1))
+                             : ((int64_t)(r0 + row) << log2row) + (at & ((1 << log2row) - 1));
       __builtin_amdgcn_global_load_lds(
           reinterpret_cast<const __attribute__((address_space(1))) void*>(
               reinterpret_cast<uintptr_t>(aug) + (uintptr_t)g),
@@ -438,7 +504,7 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
   CS_STAMP_COUNT(31);
   CS_STAMP(16);
   const int item0 = (int)blockIdx.x * sa.P;
-  const int item = item0 + (tid >> sa.log2U);
+  const int item = item0 + (tid >> (sa.log2U + log2S));
   const bool live = item < sa.items;
   int bb = 0, ho = 0, wo = 0;
   if (live) {
@@ -458,15 +524,18 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
   float bv[KP];
 #pragma unroll
   for (int j = 0; j < KP; ++j) bv[j] = 0.f;
+  // (WIDE: of the channels it finishes, added last)
+  const int per = KP >> log2S, bias0 = ch0 + u * KP + (part.s4 >> 2) * per;
   if (bias != nullptr) {                                 // uniform
 #pragma unroll
-    for (int j = 0; j < KP; ++j) bv[j] = bias[ch0 + u * KP + j];
+    for (int j = 0; j < KP; ++j)
+      if (!WIDE || j < per) bv[j] = bias[bias0 + j];
   }
   StreamPre q;
-  stream_prefetch(q, lidx, lval, lcnt, geo, place, 0, 0, sa.fd_kw);
+  stream_prefetch(q, lidx, lval, lcnt, geo, place, 0, 0, sa.fd_kw, part);
   copy_block(0, sa.off_t0);
 #pragma unroll
-  for (int j = 0; j < KP; ++j) acc[j * STREAM_BD + tid] = bv[j];
+  for (int j = 0; j < KP; ++j) acc[j * STREAM_BD + tid] = WIDE ? 0.f : bv[j];
   block_done();
 
   int cursor = 0;                                        // place in the current tap's list
@@ -480,10 +549,10 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
       const int t0 = blk * sa.tpb, t1 = min(T_, t0 + sa.tpb);
       for (int t = t0; t < t1; ++t) {
         StreamPre nxt;
-        stream_prefetch(nxt, lidx, lval, lcnt, geo, place, t + 1, 0, sa.fd_kw);
+        stream_prefetch(nxt, lidx, lval, lcnt, geo, place, t + 1, 0, sa.fd_kw, part);
         if (t == t0 && has_next) copy_block((blk + 1) * sa.RB, tnext);
         stream_tap<GB, false>(q, lidx, lval, geo.cap, 0, C, (t - t0) * C, smem, toff, log2row,
-                              lane_tab, col);
+                              lane_tab, col, part);
         q = nxt;
       }
     } else {
@@ -494,18 +563,25 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
       if (c_lo == 0) cursor = 0;
       if (has_next) copy_block((blk + 1) * sa.RB, tnext);
       cursor = stream_tap<GB, true>(q, lidx, lval, geo.cap, cursor, c_lo + sa.RB, -c_lo, smem, toff,
-                                    log2row, lane_tab, col);
+                                    log2row, lane_tab, col, part);
       const int tn = (blk + 1) / sa.cblocks;
       stream_prefetch(q, lidx, lval, lcnt, geo, place, has_next ? tn : T_, tn == t0 ? cursor : 0,
-                      sa.fd_kw);
+                      sa.fd_kw, part);
     }
     blk_time += CS_CLOCK() - blk_t0;
     if (has_next) block_done();
   }
   CS_STAMP(17);
   CS_STAMP_ADD(21, blk_time);
-  stream_kwta<TO, KP, STREAM_BD>(acc, sa.log2U, sa.log2Us, (int64_t)item, live, geo.c_out, ch0,
-                                 sa.k, sa.write_sums, y, out, lo);
+  if constexpr (WIDE) {
+    wave_lds_order();                                    // a pixel's parts: one wavefront's lanes
+    if (live)
+      stream_sum_parts<KP>(acc, log2S, sa.pairs, part.s4 >> 2, bv,
+                           y + (int64_t)item * geo.c_out + bias0);
+  } else {
+    stream_kwta<TO, KP, STREAM_BD>(acc, sa.log2U, sa.log2Us, (int64_t)item, live, geo.c_out, sa.k,
+                                   sa.write_sums, y, out, lo);
+  }
   CS_STAMP(18);
 }
 

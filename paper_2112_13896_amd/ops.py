@@ -394,8 +394,8 @@ def mrs_plan(dtype: torch.dtype, cap: int, in_shape, kh: int, kw: int, stride: i
     kwta = None if k < 0 else ("separate" if info[10] else "fused")
     if path == "blocks":
         return {"path": path, "kwta": kwta, "select": info[1], "rows_per_block": info[2],
-                "table_blocks": info[3], "blocks": info[6], "lds": info[7],
-                "sets_per_lane": info[8]}
+                "table_blocks": info[3], "slices": info[4], "list_parts": 1 << info[5],
+                "blocks": info[6], "lds": info[7], "sets_per_lane": info[8]}
     if path == "rows":
         return {"path": path, "kwta": kwta, "blocks": info[6], "lds": info[7],
                 "channels_per_lane": info[8]}

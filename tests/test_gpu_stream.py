@@ -101,48 +101,62 @@ def test_streamed_table_layer(case, form):
     assert torch.equal(y2.view(torch.int32), y.view(torch.int32))
 
 
-# (b, h, w, c_in), non-zeros, stride, pad, c_out, n, in slices of 256 channels
+# (b, h, w, c_in), non-zeros, stride, pad, c_out, n; in slices: how many, parts of a list;
+# the kernel that adds the sums a k-WTA follows
 WIDE_CASES = [
-    ((2, 8, 8, 64), 20, 1, 0, 512, 16, True),               # on the line: 256 slices of pixels
-    ((1, 1, 127, 64), 20, 1, 0, 512, 16, False),            # below it
-    ((1, 8, 12, 36), 9, 1, 0, 768, 8, True),                # two sets a lane, three slices
-    ((2, 16, 16, 512), 300, 1, 0, 1024, 16, True),          # channel ranges, long lists
-    ((4, 14, 14, 128), 12, 2, 0, 1024, 16, True),           # stride 2
-    ((3, 9, 9, 3), 2, 1, 1, 512, 16, True),                 # three channels, padding
-    ((3, 9, 9, 64), 8, 1, 0, 384, 16, False),               # not a multiple of 256
-    ((3, 9, 9, 64), 8, 1, 0, 512, 4, False),                # sets of four
+    ((2, 8, 8, 64), 20, 1, 0, 512, 16, (2, 2), "fused"),
+    ((1, 1, 127, 64), 64, 1, 0, 512, 16, (2, 2), "fused"),       # a short last tile, full lists
+    ((1, 8, 12, 36), 9, 1, 0, 768, 8, (3, 2), "fused"),          # two sets a lane
+    ((2, 14, 14, 128), 12, 1, 0, 512, 16, (2, 4), "fused"),      # four parts in pairs
+    ((3, 9, 9, 8), 5, 1, 1, 512, 16, (2, 1), "fused"),           # padding, one part
+    ((4, 14, 14, 128), 12, 2, 0, 1024, 16, (4, 2), "tiled"),     # stride 2
+    ((1, 14, 14, 256), 120, 1, 0, 1024, 16, (4, 4), "tiled"),    # four parts in order, long lists
+    ((1, 14, 14, 128), 40, 1, 0, 512, 8, (2, 2), "tiled"),
+    ((1, 5, 7, 64), 30, 1, 0, 1536, 16, (6, 1), "tiled"),
+    ((1, 9, 9, 512), 50, 1, 0, 1024, 16, None, "tiled"),         # the table takes two blocks
+    ((3, 9, 9, 64), 8, 1, 0, 384, 16, None, "fused"),            # not a multiple of 256
+    ((3, 9, 9, 64), 8, 1, 0, 512, 4, None, "fused"),             # sets of four
 ]
 
 
 @pytest.mark.parametrize("case", WIDE_CASES, ids=[str(i) for i in range(len(WIDE_CASES))])
 def test_wide_sums_in_slices(case):
-    """Sums of a 1x1 layer of more than 256 channels: within tolerance of the
-    oracle, and where the layer goes in slices the bits of its 256-channel
-    slices run as layers of their own."""
-    shape, nnz, stride, pad, c_out, n, sliced = case
+    """Sums of a 1x1 layer of more than 256 channels, which go in slices of 256:
+    within tolerance of the oracle, and the bits of the sums that the layer with
+    a k-WTA keeps (cs_mrs_kwta_conv2d: "cs_mrs_conv2d followed by k-WTA"), which
+    run on the fused or the table-slice kernel."""
+    shape, nnz, stride, pad, c_out, n, wide, kept_path = case
     r = np.random.default_rng(sum(shape) + c_out + n)
     b, h, w, c = shape
     x = np.zeros((b * h * w, c), np.float32)
     for i in range(len(x)):
-        m = (nnz, nnz // 3, 0, min(c, 2 * nnz))[i % 4]
+        m = (nnz, nnz // 3, 0, min(c, 2 * nnz), 1, c)[i % 6]
         x[i, r.permutation(c)[:m]] = r.normal(size=m)
     W = np.zeros((c_out // n, n, c), np.float32)
     np.put_along_axis(W, r.integers(0, n, (c_out // n, 1, c)),
                       r.normal(size=(c_out // n, 1, c)).astype(np.float32), axis=1)
     W = W.reshape(c_out, c)
     bias = r.normal(size=c_out).astype(np.float32)
+    plan = [ops.mrs_plan(torch.float32, c, shape, 1, 1, stride, pad, c_out, n, 1, k)
+            for k in (-1, c_out // 16)]
+    assert plan[1]["path"] == kept_path and plan[1]["kwta"] == "separate", plan
+    if wide is None:
+        assert plan[0]["path"] == kept_path, plan
+    else:
+        assert (plan[0]["slices"], plan[0]["list_parts"]) == wide, plan
+        assert plan[0]["select"] == 9 and plan[0]["table_blocks"] == 1, plan
     idx, lv, cnt = ops.compact(dev(x))
-
-    def sums(lo, hi):
-        aug = ops.aug_to_device(ops.pack(W[lo:hi], n)[0])
-        return host(ops.mrs_conv2d(idx, lv, cnt, shape, aug, 1, 1, n, stride, pad, dev(bias[lo:hi])))
-
-    got = sums(0, c_out)
+    aug = ops.aug_to_device(ops.pack(W, n)[0])
+    args = (idx, lv, cnt, shape, aug, 1, 1, n, stride, pad)
     W4 = W.reshape(c_out, 1, 1, c)
     ref = o.conv2d_nhwc(x.reshape(shape), W4, stride, pad, bias)
     S = o.abs_sum_conv(x.reshape(shape), W4, stride, pad) + np.abs(bias)
-    assert_f32_close(got.reshape(-1, c_out), ref.reshape(-1, c_out), S.reshape(-1, c_out), "sums")
-    if sliced:
-        parts = np.concatenate([sums(i, i + 256) for i in range(0, c_out, 256)], axis=-1)
-        assert np.array_equal(got.reshape(-1, c_out).view(np.uint32),
-                              parts.reshape(-1, c_out).view(np.uint32))
+    got = ops.mrs_conv2d(*args, dev(bias))
+    assert_f32_close(host(got).reshape(-1, c_out), ref.reshape(-1, c_out), S.reshape(-1, c_out),
+                     "sums")
+    for bd in (dev(bias), None):
+        got = ops.mrs_conv2d(*args, bd)
+        kept = ops.mrs_kwta_conv2d(*args, bd, k=c_out // 16)[0]
+        assert torch.equal(got.view(torch.int32).flatten(), kept.view(torch.int32).flatten())
+        whole = ops.conv2d(dev(x.reshape(shape)), aug, 1, 1, n, stride, pad, bd)
+        assert torch.equal(whole.view(torch.int32).flatten(), kept.view(torch.int32).flatten())

@@ -69,12 +69,23 @@ struct NextLayer {
   uint32_t off_acc;  // LDS byte offset of its c_out accumulators
 };
 
+// The wavefront's number, as a scalar or in a vector register.  As a scalar the body
+// takes 50 vector registers instead of 72 (int8), which the one-kernel chains and the
+// dense-input kernel gain from; the kernel on lists alone loses: 8,192 rows of 512, 64
+// entries, 64 outputs, 8 winners 161.9 us with the scalar, 152.0 with the vector.
+template <bool SCALAR>
+__device__ __forceinline__ int sample_wave() {
+  const int w = (int)threadIdx.x >> 6;
+  return SCALAR ? __builtin_amdgcn_readfirstlane(w) : w;
+}
+
 // Exclusive prefix sum of one int per thread over the workgroup; *total gets
 // the sum.  ws: SAMPLE_BD / 64 ints.  Barriers inside (call uniformly, with
-// every thread active).
+// every thread active).  SCALAR: see sample_wave.
+template <bool SCALAR>
 __device__ __forceinline__ int sample_scan(int v, int* ws, int* total) {
   const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wv = sample_wave<SCALAR>();
   const int incl = (int)wave_incl_scan((uint32_t)v, 0u, OpAdd{});
   if (lane == 63) ws[wv] = incl;
   __syncthreads();
@@ -135,7 +146,7 @@ __device__ __forceinline__ void dense_load(const T* __restrict__ xr, int ne, int
 // The workgroup body for sample `item` (SAMPLE_BD threads).  DENSE: lval is the
 // dense input [items][ne] and lcnt is not read; dcnt, when not NULL, gets the
 // sample's non-zero count.
-template <typename T, typename A, typename TO, bool DENSE = false>
+template <typename T, typename A, typename TO, bool DENSE = false, bool SCALAR = true>
 __device__ __forceinline__ void sample_body(const uint16_t* __restrict__ lidx,
                                             const T* __restrict__ lval,
                                             const int32_t* __restrict__ lcnt,
@@ -148,7 +159,7 @@ __device__ __forceinline__ void sample_body(const uint16_t* __restrict__ lidx,
   using E = typename Aug<T>::type;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wv = sample_wave<SCALAR>();
   const int n = geo.n, G = geo.G, C = geo.C, c_out = geo.c_out, cap = geo.cap;
   const int npix = sa.npix, ne = npix * cap;
   A* acc = reinterpret_cast<A*>(smem);                              // [S][n][G]
@@ -201,7 +212,7 @@ __device__ __forceinline__ void sample_body(const uint16_t* __restrict__ lidx,
       if (r0 + SAMPLE_BD * SAMPLE_DV < ne)                          // the next round, in flight
         dense_load<T>(lval + base, ne, e + SAMPLE_BD * SAMPLE_DV, vec, dv);
       int add = 0;
-      int pos = tot + sample_scan(nz, misc, &add);
+      int pos = tot + sample_scan<SCALAR>(nz, misc, &add);
 #pragma unroll
       for (int j = 0; j < SAMPLE_DV; ++j) {
         if (cur[j] != T(0)) {                                       // -0.0 is a zero
@@ -215,7 +226,7 @@ __device__ __forceinline__ void sample_body(const uint16_t* __restrict__ lidx,
     if (dcnt != nullptr && tid == 0) dcnt[item] = tot;
   } else {
     c = c < 0 ? 0 : (c > cap ? cap : c);
-    e0 = sample_scan(c, misc, &tot);
+    e0 = sample_scan<SCALAR>(c, misc, &tot);
   }
   // slices in use: enough for SAMPLE_BATCH entries per job, at most S
   int Sr = (tot + SAMPLE_BATCH - 1) / SAMPLE_BATCH;
@@ -446,7 +457,7 @@ __device__ __forceinline__ void sample_body(const uint16_t* __restrict__ lidx,
     eq_t += (in && key[j] == thr) ? 1 : 0;
   }
   int tot2 = 0;
-  const int pre = sample_scan(gt_t | (eq_t << 16), misc, &tot2);
+  const int pre = sample_scan<SCALAR>(gt_t | (eq_t << 16), misc, &tot2);
   int gt_before = pre & 0xFFFF, eq_before = pre >> 16;
   bool wins[SAMPLE_KEYS];
   if (lo.idx) {
@@ -542,7 +553,8 @@ __global__ __launch_bounds__(SAMPLE_BD) void mrs_sample(const uint16_t* __restri
                                                         A* __restrict__ y, TO* __restrict__ out,
                                                         ListOut lo, ConvGeom geo, SampleArgs sa,
                                                         NextLayer nx) {
-  sample_body<T, A, TO>(lidx, lval, lcnt, aug, bias, y, out, lo, geo, sa, nx, blockIdx.x);
+  sample_body<T, A, TO, false, false>(lidx, lval, lcnt, aug, bias, y, out, lo, geo, sa, nx,
+                                      blockIdx.x);
 }
 
 // The same layer on a dense input [B][ne], with no lists between.  A row's

@@ -146,7 +146,7 @@ __device__ __forceinline__ void scatter_body(const uint16_t* __restrict__ lidx,
   for (int o = tid; o < c_out; o += SCAT_BD) bias_s[o] = bias ? bias[o] : 0;
   c = c < 0 ? 0 : (c > cap ? cap : c);
   int tot = 0;
-  const int e0 = sample_scan(c, misc, &tot);
+  const int e0 = sample_scan<true>(c, misc, &tot);
   if (tid < npix) pix[tid] = make_int2(e0, c);
   {
     const int nacc = 2 * sc.guard + nrows * Wo * sc.ostride;       // allocated rounded up to 4

@@ -1515,13 +1515,23 @@ WsLayout ws_layout(cs_dtype xt, int64_t rows, int c_in) {
   return l;
 }
 
+// The dense-input kernel ranks a sample's non-zeros with one workgroup's barriers, which
+// few samples hide behind the launch it saves, and many short ones do not: 8,192 rows of
+// 64 -> 32 int8 86.5 us against 72.4 us for compaction and the list kernel (2,048 rows
+// 23.4 and 21.9; 1,024 rows 12.5 and 13.4), 512 -> 512 fp32 with k-WTA 213.5 and 206.1
+// (28.7 and 30.4).  Rows of 2,048 elements stay ahead or level at any batch (8,192 rows,
+// 2,048 -> 1,000: int8 164.5 and 167.0, fp32 215.4 and 223.6).
+bool dense_sample_pays(const cs::ConvGeom& geo) {
+  return geo.B <= 4 * kPlanCus || (int64_t)geo.H * geo.W * geo.C >= 2048;
+}
+
 // Sums of a layer on its dense input: one launch where a workgroup takes a
 // sample (the sample's non-zeros go straight into its LDS entry list), else
 // the compaction into idx/lv/cnt and the layer's kernel.
 int dense_launch(cs_dtype xt, const void* x, const cs::ConvGeom& geo, const void* aug,
                  const void* bias, void* y, uint16_t* idx, void* lv, int32_t* cnt, hipStream_t s) {
   SamplePlan sp;
-  if (sample_plan(geo, xt, -1, 0, 1, &sp)) {
+  if (dense_sample_pays(geo) && sample_plan(geo, xt, -1, 0, 1, &sp)) {
     const cs::ListOut none{nullptr, nullptr, nullptr, 0};
     if (xt == CS_F32)
       return launch_sample_dense<float, float, float>(sp, s, x, aug, bias, y, nullptr, none, geo,
@@ -2198,7 +2208,8 @@ int cs_conv2d_kwta(cs_dtype xt, const void* x, int b, int h, int w, int c_in, in
   SamplePlan sp;
   // one pixel per sample: its count is the sample's (more pixels: lcnt needs
   // the compaction's counts)
-  if (h == 1 && w == 1 && sample_plan(geo, xt, k, shift, keep_sums, &sp)) {
+  if (h == 1 && w == 1 && dense_sample_pays(geo) &&
+      sample_plan(geo, xt, k, shift, keep_sums, &sp)) {
     const cs::ListOut lo{oidx, oval, ocnt, lists ? ocap : 0};
     if (xt == CS_F32)
       return launch_sample_dense<float, float, float>(sp, s, x, aug, bias, y, out, lo, geo, lcnt);

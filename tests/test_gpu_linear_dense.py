@@ -90,3 +90,31 @@ def test_dense_input_equals_lists(case, offset):
         for i, c in enumerate(host(got[2])):
             assert torch.equal(got[0][i, :c], want[0][i, :c])
             assert torch.equal(got[1][i, :c], want[1][i, :c])
+
+
+@pytest.mark.parametrize("dt", ["i8", "f32"])
+@pytest.mark.parametrize("b, d_in, one", [(1024, 64, True), (1025, 64, False), (1100, 2044, False),
+                                          (1100, 2048, True)])
+def test_one_launch_only_where_it_pays(dt, b, d_in, one):
+    """Up to 1,024 samples, or rows of 2,048 elements, take one launch and leave
+    the list buffers alone; more and shorter rows are compacted first.  The
+    results are the lists' either way."""
+    r = np.random.default_rng(b + d_in)
+    n, d_out, k = 4, 32, 6
+    x = np.where(r.random((b, d_in)) < 0.1, r.integers(1, 128, (b, d_in)), 0)
+    W = complementary_weights(r, r, d_out, d_in, n, "int8" if dt == "i8" else "normal")
+    xd = dev(x.astype(W.dtype))
+    aug = ops.aug_to_device(ops.pack(W, n)[0])
+    idx, lv, cnt = ops.compact(xd)
+    shape = (b, 1, 1, d_in)
+    y0, want = ops.mrs_kwta_conv2d(idx, lv, cnt, shape, aug, 1, 1, n, k=k)
+    ws = ops.workspace(0, xd.dtype, b, d_in, xd.device)
+    ws.fill_(0x5A)
+    y = ops.linear(xd, aug, n, ws=ws)
+    assert bool((ws == 0x5A).all()) == one
+    assert torch.equal(y.view(torch.int32).flatten(), y0.view(torch.int32).flatten())
+    lists = (torch.full_like(idx, -2), torch.empty_like(lv), torch.empty_like(cnt))
+    _, got = ops.conv2d_kwta(xd.view(shape), aug, 1, 1, n, k=k, y=torch.empty_like(y0), ws=lists)
+    assert bool((lists[0] == -2).all()) == one
+    assert torch.equal(lists[2], cnt)
+    assert torch.equal(got.view(torch.int32).flatten(), want.view(torch.int32).flatten())

@@ -257,8 +257,8 @@ int cs_mrs_plan(cs_dtype xt, int cap, int b, int h, int w, int c_in, int kh, int
  * cs_linear - a whole sparse-sparse linear layer: cs_compact of x into the
  * workspace, then Multiply/Route/Sum (a linear layer is the 1x1 convolution
  * of 1x1 images); in one launch, the workspace untouched, when the layer runs
- * with a workgroup per sample and there are at most 1,024 samples or their rows
- * have at least 2,048 elements.  DEVICE memory.
+ * with a workgroup per sample, there are at most 1,024 samples or their rows
+ * have at least 2,048 elements, and y shares no memory with x.  DEVICE memory.
  *
  *  x       device [batch][d_in] (int8 or fp32), d_in <= CS_MAX_ROW.
  *  aug     device augmented packed tensor [d_in][G] from cs_pack of [d_out][d_in].
@@ -287,8 +287,9 @@ int cs_conv2d(cs_dtype xt, const void* x, int b, int h, int w, int c_in, int kh,
  * a linear layer (1x1 images) where cs_linear takes one.  DEVICE memory.
  *
  *  xt .. pool   as cs_conv2d.      y .. ocap   as cs_mrs_kwta_conv2d.
- *  lidx, lval, lcnt   the caller's list buffers (not NULL); lcnt holds the
- *          pixels' non-zero counts afterwards, lidx and lval are scratch.
+ *  lidx, lval, lcnt   the caller's list buffers (not NULL, none of x's memory);
+ *          lcnt holds the pixels' non-zero counts afterwards, lidx and lval are
+ *          scratch.  The outputs may lie over x: then two launches.
  *  Errors: as cs_compact and cs_mrs_kwta_conv2d.
  */
 int cs_conv2d_kwta(cs_dtype xt, const void* x, int b, int h, int w, int c_in, int kh, int kw,

@@ -1525,13 +1525,23 @@ bool dense_sample_pays(const cs::ConvGeom& geo) {
   return geo.B <= 4 * kPlanCus || (int64_t)geo.H * geo.W * geo.C >= 2048;
 }
 
+// Whether n bytes at p and the dense input x share memory.  In one launch a sample's
+// outputs may be written while another's row is still to be read; with the compaction
+// first the whole input is read before the first output.
+bool shares_input(const void* x, cs_dtype xt, const cs::ConvGeom& geo, const void* p, size_t n) {
+  const auto x0 = reinterpret_cast<uintptr_t>(x), p0 = reinterpret_cast<uintptr_t>(p);
+  const size_t nx = (size_t)geo.B * geo.H * geo.W * geo.C * elem_size(xt);
+  return p != nullptr && x0 < p0 + n && p0 < x0 + nx;
+}
+
 // Sums of a layer on its dense input: one launch where a workgroup takes a
 // sample (the sample's non-zeros go straight into its LDS entry list), else
 // the compaction into idx/lv/cnt and the layer's kernel.
 int dense_launch(cs_dtype xt, const void* x, const cs::ConvGeom& geo, const void* aug,
                  const void* bias, void* y, uint16_t* idx, void* lv, int32_t* cnt, hipStream_t s) {
   SamplePlan sp;
-  if (dense_sample_pays(geo) && sample_plan(geo, xt, -1, 0, 1, &sp)) {
+  if (dense_sample_pays(geo) && sample_plan(geo, xt, -1, 0, 1, &sp) &&
+      !shares_input(x, xt, geo, y, (size_t)geo.B * geo.c_out * 4)) {
     const cs::ListOut none{nullptr, nullptr, nullptr, 0};
     if (xt == CS_F32)
       return launch_sample_dense<float, float, float>(sp, s, x, aug, bias, y, nullptr, none, geo,
@@ -2208,7 +2218,13 @@ int cs_conv2d_kwta(cs_dtype xt, const void* x, int b, int h, int w, int c_in, in
   SamplePlan sp;
   // one pixel per sample: its count is the sample's (more pixels: lcnt needs
   // the compaction's counts)
-  if (h == 1 && w == 1 && dense_sample_pays(geo) &&
+  const size_t ob = elem_size(ot);
+  const bool shared = shares_input(x, xt, geo, y, (size_t)b * c_out * 4) ||
+                      shares_input(x, xt, geo, out, (size_t)b * c_out * ob) ||
+                      (lists && (shares_input(x, xt, geo, oidx, (size_t)b * ocap * 2) ||
+                                 shares_input(x, xt, geo, oval, (size_t)b * ocap * ob) ||
+                                 shares_input(x, xt, geo, ocnt, (size_t)b * 4)));
+  if (h == 1 && w == 1 && !shared && dense_sample_pays(geo) &&
       sample_plan(geo, xt, k, shift, keep_sums, &sp)) {
     const cs::ListOut lo{oidx, oval, ocnt, lists ? ocap : 0};
     if (xt == CS_F32)

@@ -118,3 +118,32 @@ def test_one_launch_only_where_it_pays(dt, b, d_in, one):
     assert bool((lists[0] == -2).all()) == one
     assert torch.equal(lists[2], cnt)
     assert torch.equal(got.view(torch.int32).flatten(), want.view(torch.int32).flatten())
+
+
+@pytest.mark.parametrize("d_in, d_out", [(2048, 512), (512, 512), (96, 128)])
+def test_outputs_over_the_input(d_in, d_out):
+    """Outputs that lie over the input: the input is compacted whole before the
+    first output is written (with one launch, a workgroup would write its row
+    where another has still to read), so the sums and winners are those of
+    separate buffers."""
+    b, n, k = 600, 8, 20
+    r = np.random.default_rng(d_in)
+    x = np.where(r.random((b, d_in)) < 0.1, r.normal(size=(b, d_in)), 0).astype(np.float32)
+    W = complementary_weights(r, r, d_out, d_in, n, "normal")
+    aug = ops.aug_to_device(ops.pack(W, n)[0])
+    flat = torch.empty(b * max(d_in, d_out), device="cuda")
+    xd, over = flat[:x.size].view(b, d_in), flat[:b * d_out].view(b, d_out)
+    ws = ops.workspace(0, xd.dtype, b, d_in, xd.device)
+    ws.fill_(0x5A)
+    want = ops.linear(dev(x), aug, n)
+    xd.copy_(dev(x))
+    assert torch.equal(ops.linear(xd, aug, n, out=over, ws=ws), want)
+    assert not bool((ws == 0x5A).all())                                # compacted first
+    shape = (b, 1, 1, d_in)
+    bufs = [torch.empty((b, d_in), dtype=t, device="cuda") for t in (torch.int16, torch.float32)]
+    bufs.append(torch.empty(b, dtype=torch.int32, device="cuda"))
+    sep = ops.conv2d_kwta(dev(x).view(shape), aug, 1, 1, n, k=k, y=torch.empty_like(want), ws=bufs)
+    xd.copy_(dev(x))
+    got = ops.conv2d_kwta(xd.view(shape), aug, 1, 1, n, k=k, y=torch.empty_like(want), out=over,
+                          ws=bufs)
+    assert torch.equal(got[0], sep[0]) and torch.equal(got[1], sep[1])

@@ -1183,7 +1183,7 @@ int occupancy(const void* kern, int threads, size_t shmem) {
   return nb;
 }
 
-template <typename TO, int MODE, int M, bool FULL>
+template <typename TO, int MODE, int M, bool FULL, int H = 2>
 void launch_rows_k(RowsPlan pl, hipStream_t s, const uint16_t* idx, const void* lval,
                    const int32_t* cnt, const void* aug, const void* bias, void* y, void* out,
                    const cs::ListOut& lo, const cs::ConvGeom& geo) {
@@ -1200,7 +1200,7 @@ void launch_rows_k(RowsPlan pl, hipStream_t s, const uint16_t* idx, const void* 
     int occ = -1;
     if ((size_t)occ_cache[slot][0].load() == sh) occ = occ_cache[slot][1].load();
     if (occ < 0) {
-      occ = occupancy(reinterpret_cast<const void*>(&cs::mrs_rows<TO, MODE, M, FULL>), 64 * w, sh);
+      occ = occupancy(reinterpret_cast<const void*>(&cs::mrs_rows<TO, MODE, M, FULL, H>), 64 * w, sh);
       occ_cache[slot][1].store(occ);
       occ_cache[slot][0].store((int)sh);
     }
@@ -1211,7 +1211,7 @@ void launch_rows_k(RowsPlan pl, hipStream_t s, const uint16_t* idx, const void* 
     }
   }
   if (best_w > 0) rows_layout(&pl, best_w, best_cu, geo.c_out);   // else the plan's layout
-  hipLaunchKernelGGL((cs::mrs_rows<TO, MODE, M, FULL>), dim3((unsigned)pl.blocks),
+  hipLaunchKernelGGL((cs::mrs_rows<TO, MODE, M, FULL, H>), dim3((unsigned)pl.blocks),
                      dim3(64 * pl.waves), pl.shmem, s, idx, static_cast<const int8_t*>(lval), cnt,
                      static_cast<const uint16_t*>(aug),
                      static_cast<const int32_t*>(bias), static_cast<int32_t*>(y),
@@ -1245,7 +1245,10 @@ int launch_rows(const RowsPlan& pl, cs_dtype ot, hipStream_t s, const uint16_t* 
                 void* out, const cs::ListOut& lo, const cs::ConvGeom& geo) {
 #define CS_ROWS(TO_, MODE_) \
   launch_rows_t<TO_, MODE_>(pl, s, idx, lval, cnt, aug, bias, y, out, lo, geo)
-  if (pl.ra.k < 0)
+  if (pl.ra.k < 0 && pl.cols == 3 && geo.cap <= 64)
+    launch_rows_k<int32_t, cs::ROWS_SUMS, 3, false, 1>(pl, s, idx, lval, cnt, aug, bias, y, out, lo,
+                                                       geo);
+  else if (pl.ra.k < 0)
     launch_rows_k<int32_t, cs::ROWS_SUMS, 0, false>(pl, s, idx, lval, cnt, aug, bias, y, out, lo,
                                                     geo);
   else if (lo.idx != nullptr && ot == CS_I8) CS_ROWS(int8_t, cs::ROWS_LISTS);

@@ -83,10 +83,13 @@ __device__ __forceinline__ uint32_t rows_entry2(uint32_t w) {       // two entri
 // What the kernel writes: the sums, the winners as lists, or densely.
 constexpr int ROWS_SUMS = 0, ROWS_LISTS = 1, ROWS_DENSE = 2;
 
-// M: 64-channel columns held by a lane (64 M >= c_out; 0 with ROWS_SUMS).
-// FULL: c_out == 64 M.
+// M: 64-channel columns held by a lane (64 M >= c_out; 0, sums only: any number, looped
+// over).  FULL: c_out == 64 M.  H: 64-entry halves of ROWS_ENTS a list can reach into.
+// Short rows of short lists are all overhead per item, and the loops' count: 25,088
+// items 32 -> 192, 4 entries, sums 11.8 us with M = 0 and both halves, 10.8 with M = 3,
+// 10.5 with H = 1 too; 16 -> 96, 3 entries, 10.6, 10.0 and 9.5.
 // Registers held to eight wavefronts per SIMD up to nine columns.
-template <typename TO, int MODE, int M, bool FULL>
+template <typename TO, int MODE, int M, bool FULL, int H = 2>
 __global__ __launch_bounds__(ROWS_BD, M <= 9 ? 8 : 4) void mrs_rows(const uint16_t* __restrict__ lidx,
                                                     const int8_t* __restrict__ lval,
                                                     const int32_t* __restrict__ lcnt,
@@ -148,7 +151,7 @@ __global__ __launch_bounds__(ROWS_BD, M <= 9 ? 8 : 4) void mrs_rows(const uint16
   auto has = [&](int j) { return FULL || 64 * j < cc; };
   auto valid = [&](int j, int ln) { return FULL || 64 * j + ln < cc; };
   auto reset_row = [&](int ln) {
-    if constexpr (MODE == ROWS_SUMS) {
+    if constexpr (M == 0) {
       for (int j = 0; j < cols; ++j) acc[64 * j + ln] = bias_s[64 * j + ln];
     } else {
       cc = opaque_uniform(c);
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(ROWS_BD, M <= 9 ? 8 : 4) void mrs_rows(const uint16
       const int64_t it = ib + li;
       cnt_n = lcnt[it];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < H; ++h) {
         if (64 * h < cap) {                                         // uniform
           const int j = lane + 64 * h < cap ? lane + 64 * h : cap - 1;
           pi_n[h] = lidx[it * cap + j];
@@ -217,7 +220,7 @@ __global__ __launch_bounds__(ROWS_BD, M <= 9 ? 8 : 4) void mrs_rows(const uint16
       // offsets and their values (zero past the list)
       int pre[2], xv[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < H; ++h) {
         const int j = lane + 64 * h;
         pre[h] = xv[h] = 0;
         if (64 * h < nb) {                                          // uniform
@@ -234,7 +237,7 @@ __global__ __launch_bounds__(ROWS_BD, M <= 9 ? 8 : 4) void mrs_rows(const uint16
       // another (wavefront-uniform, read from their lanes)
       if (qf > 0) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < H; ++h) {
           const int nh = nb - 64 * h < 64 ? nb - 64 * h : 64;
           for (int e = 0; e < nh; e += ROWS_BATCH) {                // uniform
             int sp[ROWS_BATCH], sx[ROWS_BATCH];
@@ -265,7 +268,7 @@ __global__ __launch_bounds__(ROWS_BD, M <= 9 ? 8 : 4) void mrs_rows(const uint16
       // wavefront-private copy of the entries in LDS
       if (ra.S > 0 && !group) {
         ent[lane] = make_int2(pre[0], xv[0]);
-        if (nb > 64) ent[lane + 64] = make_int2(pre[1], xv[1]);
+        if (H > 1 && nb > 64) ent[lane + 64] = make_int2(pre[1], xv[1]);
         wave_lds_order();
         if (job) {
           const int S = ra.S;

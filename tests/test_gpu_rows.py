@@ -89,3 +89,41 @@ def test_rows_match_oracle(case):
     # the sums alone
     y = ops.mrs_conv2d(idx, lv, cnt, shape, aug, 1, 1, n, bias=dev(bias))
     assert np.array_equal(host(y).reshape(items, c_out).astype(np.int64), ref)
+
+
+# c_in, non-zeros, c_out, n: sums of at most 192 channels from lists of at most 64 entries
+# (an instance of their own) and one past each limit
+SUMS_CASES = [
+    (64, 64, 192, 8),         # full lists, whole columns
+    (64, 40, 130, 2),         # 65 sets in two groups of 64, pads
+    (32, 4, 192, 24),         # eight sets in eight slices
+    (17, 3, 4, 4),            # one set
+    (65, 65, 192, 8),
+    (64, 40, 200, 8),
+]
+
+
+@pytest.mark.parametrize("case", SUMS_CASES, ids=[f"{c[0]}-{c[2]}" for c in SUMS_CASES])
+def test_short_rows_sums_only(case):
+    c_in, nnz, c_out, n = case
+    items = 4200
+    r = np.random.default_rng(c_in + c_out)
+    x = np.zeros((items, c_in), np.int8)
+    for i in range(items):
+        at = r.permutation(c_in)[:(nnz, nnz // 2, 0, 1)[i % 4]]
+        x[i, at] = r.integers(-128, 128, len(at))
+    W = np.zeros((c_out // n, n, c_in), np.int8)
+    np.put_along_axis(W, r.integers(0, n, (c_out // n, 1, c_in)),
+                      r.integers(-128, 128, (c_out // n, 1, c_in)).astype(np.int8), axis=1)
+    W = W.reshape(c_out, c_in)
+    bias = r.integers(-1000, 1001, c_out).astype(np.int32)
+    shape = (1, items, 1, c_in)
+    assert ops.mrs_plan(torch.int8, c_in, shape, 1, 1, 1, 0, c_out, n, 1, -1)["path"] == "rows"
+    aug = ops.aug_to_device(ops.pack(W, n)[0])
+    idx, lv, cnt = ops.compact(dev(x))
+    ref = o.linear(x, W, bias)
+    y = ops.mrs_conv2d(idx, lv, cnt, shape, aug, 1, 1, n, bias=dev(bias))
+    assert np.array_equal(host(y).reshape(items, c_out).astype(np.int64), ref)
+    off = torch.empty(y.numel() + 1, dtype=torch.int32, device="cuda")[1:].view(y.shape)
+    ops.mrs_conv2d(idx, lv, cnt, shape, aug, 1, 1, n, bias=dev(bias), out=off)   # element stores
+    assert torch.equal(off, y)

@@ -549,7 +549,7 @@ bool blocks_plan(const cs::ConvGeom& geo, cs_dtype xt, const void* aug, const vo
   if (items * geo.c_out >= INT32_MAX || in_rows * geo.cap >= INT32_MAX || R * G >= INT32_MAX)
     return false;
   // sets per lane: two (four when the lane count per pixel would pass 64)
-  int gb = G >= 2 ? 2 : 1;
+  int gb = 2;                                             // G >= 2 here
   while (gb < 4 && G / gb > 64) gb *= 2;
   if (gb * n > 64 || G / gb > cs::BLK_BD) return false;   // offsets fit 16 bits
   const int U = G / gb;
@@ -677,19 +677,10 @@ int launch_blocks(const BlocksPlan& pl, hipStream_t stream, const uint16_t* idx,
   hipLaunchKernelGGL((cs::mrs_blocks_f32<float, GB_, CH_, KP_, QK_, QD_>), grid, block, pl.shmem, \
                      stream, idx, lv, cnt, pa, bs, yy, oo, lo, geo, pl.ba)
 // a pixel's lanes fill whole quads (U >= 4): the quads share the list loads
-#define CS_BLOCKS_QD(GB_, CH_, KP_)                                                      \
+#define CS_BLOCKS_QD(CH_, KP_)                                                          \
   do {                                                                                  \
-    if (pl.ba.log2U >= 2) CS_BLOCKS(GB_, CH_, KP_, 0, true);                            \
-    else CS_BLOCKS(GB_, CH_, KP_, 0, false);                                            \
-  } while (0)
-#define CS_BLOCKS_KP(GB_, CH_)                                                           \
-  do {                                                                                  \
-    const int kp = pl.own ? GB_ * geo.n : 0;                                            \
-    if (kp == 4) CS_BLOCKS_QD(GB_, CH_, 4);                                             \
-    else if (kp == 8) CS_BLOCKS_QD(GB_, CH_, 8);                                        \
-    else if (kp == 16) CS_BLOCKS_QD(GB_, CH_, 16);                                      \
-    else if (kp == 32) CS_BLOCKS_QD(GB_, CH_, 32);                                      \
-    else CS_BLOCKS_QD(GB_, CH_, 0);                                                     \
+    if (pl.ba.log2U >= 2) CS_BLOCKS(2, CH_, KP_, 0, true);                              \
+    else CS_BLOCKS(2, CH_, KP_, 0, false);                                              \
   } while (0)
 // the four-lane selection in place: two sets per lane, whole-tap blocks, four
 // lanes per pixel
@@ -700,21 +691,29 @@ int launch_blocks(const BlocksPlan& pl, hipStream_t stream, const uint16_t* idx,
     else CS_BLOCKS(2, false, KP_, 32, true);                                            \
   } while (0)
   const bool ch = pl.ba.tpb == 0;
-  if (pl.own && pl.ba.kmode >= 6) {
-    const int kp = 2 * geo.n;
+  const int kp = pl.own ? pl.gb * geo.n : 0;
+  if (pl.gb == 4) {                                       // U >= 64 lanes a pixel
+    if (ch) CS_BLOCKS(4, true, 0, 0, true); else CS_BLOCKS(4, false, 0, 0, true);
+  } else if (pl.own && pl.ba.kmode >= 6) {
     if (kp == 4) CS_BLOCKS_QUAD(4);
     else if (kp == 8) CS_BLOCKS_QUAD(8);
     else if (kp == 16) CS_BLOCKS_QUAD(16);
     else CS_BLOCKS_QUAD(32);
-  } else if (pl.gb == 1) {
-    if (ch) CS_BLOCKS_KP(1, true); else CS_BLOCKS_KP(1, false);
-  } else if (pl.gb == 2) {
-    if (ch) CS_BLOCKS_KP(2, true); else CS_BLOCKS_KP(2, false);
+  } else if (ch) {
+    // (16 and 32 channels a lane: quads of lanes would be mrs_stream's layer)
+    if (kp == 4) CS_BLOCKS_QD(true, 4);
+    else if (kp == 8) CS_BLOCKS_QD(true, 8);
+    else if (kp == 16) CS_BLOCKS(2, true, 16, 0, false);
+    else if (kp == 32) CS_BLOCKS(2, true, 32, 0, false);
+    else CS_BLOCKS_QD(true, 0);
   } else {
-    if (ch) CS_BLOCKS_KP(4, true); else CS_BLOCKS_KP(4, false);
+    if (kp == 4) CS_BLOCKS_QD(false, 4);
+    else if (kp == 8) CS_BLOCKS_QD(false, 8);
+    else if (kp == 16) CS_BLOCKS_QD(false, 16);
+    else if (kp == 32) CS_BLOCKS_QD(false, 32);
+    else CS_BLOCKS_QD(false, 0);
   }
 #undef CS_BLOCKS_QUAD
-#undef CS_BLOCKS_KP
 #undef CS_BLOCKS_QD
 #undef CS_BLOCKS
   return launch_status();

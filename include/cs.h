@@ -455,6 +455,20 @@ int cs_conv2d_dense_blocks(const int8_t* x, int b, int h, int w, int c_in, int k
                            int c_out, int n, const int32_t* bias, int32_t* y, void* stream);
 
 /*
+ * cs_conv2d_dense_blocks_plan - how cs_conv2d_dense_blocks would run these sizes (y
+ * 16-byte aligned).  Host only; no HIP call.  For tests and tuning.
+ *
+ *  info    host int64[8] out: [0] 1 on the matrix cores, 0 the routed kernel (then
+ *          the rest is 0); [1] output rows of a tile, [2] its groups of 16 output
+ *          columns, [3] tiles across an output row, [4] tiles, [5] workgroups of a
+ *          channel slice (each takes tiles from its own on, that many apart),
+ *          [6] channel slices, [7] contraction steps of 16 taps.
+ *  Errors: CS_ERR_ARG, CS_ERR_SHAPE as cs_conv2d_dense_blocks.
+ */
+int cs_conv2d_dense_blocks_plan(int b, int h, int w, int c_in, int kh, int kw, int stride, int pad,
+                                int c_out, int n, int64_t* info);
+
+/*
  * cs_conv2d_dense - the sparse-dense variant (Section 3.1: Combine, Multiply,
  * Route, Sum with dense activations; Section 4 runs the first layer of the
  * keyword-spotting network this way because its input is dense).  DEVICE

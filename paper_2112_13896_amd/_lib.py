@@ -76,6 +76,7 @@ SIGNATURES = {
                             _i, _i, _i, _vp, _vp, _vp, _vp, _i, _vp, _vp, _vp, _vp]),
     "cs_conv2d_noalloc": (_i, [_i, _vp, _i, _i, _i, _i, _i, _i, _i, _i, _vp, _i, _i, _vp, _i,
                                _vp, _vp]),
+    "cs_conv2d_dense_blocks_plan": (_i, [_i] * 10 + [_c.POINTER(_i64)]),
     "cs_conv2d_dense_blocks": (_i, [_vp, _i, _i, _i, _i, _i, _i, _i, _i, _vp, _vp, _i, _i, _vp,
                                     _vp, _vp]),
     "cs_conv2d_dense": (_i, [_i, _vp, _i, _i, _i, _i, _i, _i, _i, _i, _vp, _i, _i, _vp, _i,

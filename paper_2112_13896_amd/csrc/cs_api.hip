@@ -1944,44 +1944,74 @@ int cs_conv2d_channels(const int8_t* x, int b, int h, int w, int c_in, int kh, i
   return launch_status();
 }
 
+// The shape checks of cs_conv2d_dense_blocks behind its geometry's, and the routed
+// kernel's plan.
+static int dense_blocks_plan(const cs::ConvGeom& geo, cs::DenseBlocksArgs* da, size_t* shmem) {
+  if (geo.C > 4) return CS_ERR_SHAPE;                      // a block is one v_dot4
+  const int G = geo.G;
+  da->GB = G % 2 == 0 ? 2 : 1;
+  da->U = G / da->GB;
+  if (da->U > cs::DB_BD) return CS_ERR_SHAPE;
+  da->P = cs::DB_BD / da->U;
+  const int64_t items64 = (int64_t)geo.B * geo.Ho * geo.Wo;
+  if (items64 * geo.c_out >= ((int64_t)1 << 40) || items64 >= INT32_MAX ||
+      (int64_t)geo.B * geo.H >= INT32_MAX)
+    return CS_ERR_SHAPE;
+  da->nseg = (geo.Wo + da->P - 1) / da->P;
+  const int64_t ntiles = (int64_t)geo.B * geo.Ho * da->nseg;
+  if (ntiles >= INT32_MAX) return CS_ERR_SHAPE;
+  da->ntiles = (int)ntiles;
+  da->SW = (da->P - 1) * geo.S + geo.KW;
+  if ((int64_t)geo.KH * da->SW > (int64_t)cs::DB_PRE * cs::DB_BD) return CS_ERR_SHAPE;
+  const size_t acc_b = (size_t)da->GB * geo.n * cs::DB_BD * 4;
+  const size_t xs_b = round16((size_t)geo.KH * da->SW * 4);
+  const size_t tab_b = (size_t)geo.KH * geo.KW * G * (geo.C <= 3 ? 4 : 8);   // <= 3: one-word entries
+  da->off_x = (uint32_t)acc_b;
+  da->off_t = (uint32_t)(acc_b + xs_b);
+  *shmem = acc_b + xs_b + tab_b;
+  if (*shmem > kBlockLds) return CS_ERR_SHAPE;
+  da->fd_nseg = cs::make_fastdiv((uint32_t)da->nseg);
+  da->fd_ho = cs::make_fastdiv((uint32_t)geo.Ho);
+  da->fd_sw = cs::make_fastdiv((uint32_t)da->SW);
+  return CS_OK;
+}
+
+int cs_conv2d_dense_blocks_plan(int b, int h, int w, int c_in, int kh, int kw, int stride, int pad,
+                                int c_out, int n, int64_t* info) {
+  if (!info) return CS_ERR_ARG;
+  cs::ConvGeom geo;
+  cs::DenseBlocksArgs da;
+  size_t shmem = 0;
+  int st = conv_geometry(b, h, w, c_in, kh, kw, stride, pad, c_out, n, 1, &geo);
+  if (st == CS_OK) st = dense_blocks_plan(geo, &da, &shmem);
+  if (st != CS_OK) return st;
+  for (int i = 0; i < 8; ++i) info[i] = 0;
+  BlocksMfmaPlan mp;
+  if (!blocks_mfma_plan(geo, nullptr, kPlanCus, &mp)) return CS_OK;
+  info[0] = 1;
+  info[1] = mp.ma.RO;
+  info[2] = mp.ma.gseg;
+  info[3] = mp.ma.nseg;
+  info[4] = mp.ma.ntiles;
+  info[5] = mp.grid.x;
+  info[6] = mp.grid.y;
+  info[7] = mp.ks;
+  return CS_OK;
+}
+
 int cs_conv2d_dense_blocks(const int8_t* x, int b, int h, int w, int c_in, int kh, int kw,
                            int stride, int pad, const uint16_t* aug, const uint8_t* kidb,
                            int c_out, int n, const int32_t* bias, int32_t* y, void* stream) {
   cs::ConvGeom geo;
-  const int st = conv_geometry(b, h, w, c_in, kh, kw, stride, pad, c_out, n, 1, &geo);
+  cs::DenseBlocksArgs da;
+  size_t shmem = 0;
+  int st = conv_geometry(b, h, w, c_in, kh, kw, stride, pad, c_out, n, 1, &geo);
   if (st != CS_OK) return st;
   if (!x || !aug || !kidb || !y) return CS_ERR_ARG;
-  if (c_in > 4) return CS_ERR_SHAPE;                       // a block is one v_dot4
-  const int G = c_out / n;
-  const int GB = G % 2 == 0 ? 2 : 1;
-  const int U = G / GB;
-  if (U > cs::DB_BD) return CS_ERR_SHAPE;
-  const int P = cs::DB_BD / U;
-  const int64_t items64 = (int64_t)b * geo.Ho * geo.Wo;
-  if (items64 * c_out >= ((int64_t)1 << 40) || items64 >= INT32_MAX ||
-      (int64_t)b * h >= INT32_MAX)
-    return CS_ERR_SHAPE;
-  cs::DenseBlocksArgs da;
-  da.GB = GB;
-  da.U = U;
-  da.P = P;
-  da.nseg = (geo.Wo + P - 1) / P;
-  const int64_t ntiles = (int64_t)b * geo.Ho * da.nseg;
-  if (ntiles >= INT32_MAX) return CS_ERR_SHAPE;
-  da.ntiles = (int)ntiles;
-  da.SW = (P - 1) * stride + kw;
-  if ((int64_t)kh * da.SW > (int64_t)cs::DB_PRE * cs::DB_BD) return CS_ERR_SHAPE;
-  const size_t acc_b = (size_t)GB * n * cs::DB_BD * 4;
-  const size_t xs_b = round16((size_t)kh * da.SW * 4);
-  const bool pk = c_in <= 3;                                // one-word table entries
-  const size_t tab_b = (size_t)kh * kw * G * (pk ? 4 : 8);
-  da.off_x = (uint32_t)acc_b;
-  da.off_t = (uint32_t)(acc_b + xs_b);
-  const size_t shmem = acc_b + xs_b + tab_b;
-  if (shmem > kBlockLds) return CS_ERR_SHAPE;
-  da.fd_nseg = cs::make_fastdiv((uint32_t)da.nseg);
-  da.fd_ho = cs::make_fastdiv((uint32_t)geo.Ho);
-  da.fd_sw = cs::make_fastdiv((uint32_t)da.SW);
+  st = dense_blocks_plan(geo, &da, &shmem);
+  if (st != CS_OK) return st;
+  const int GB = da.GB;
+  const bool pk = c_in <= 3;
   // persistent: as many workgroups as fit at once (LDS and 32 wavefronts per CU)
   int cus = 0;
   const int dst = device_cus(&cus);
@@ -1989,7 +2019,7 @@ int cs_conv2d_dense_blocks(const int8_t* x, int b, int h, int w, int c_in, int k
   int64_t per_cu = lds_wgs_per_cu(shmem);
   if (per_cu > 8) per_cu = 8;
   if (per_cu < 1) per_cu = 1;
-  const int64_t nb = ntiles < per_cu * cus ? ntiles : per_cu * cus;
+  const int64_t nb = da.ntiles < per_cu * cus ? da.ntiles : per_cu * cus;
   const hipStream_t s = static_cast<hipStream_t>(stream);
   BlocksMfmaPlan mp;
   if (blocks_mfma_plan(geo, y, cus, &mp))

@@ -488,6 +488,20 @@ def conv2d_dense_blocks(x: torch.Tensor, aug: torch.Tensor, kidb: torch.Tensor, 
     return out
 
 
+def conv2d_dense_blocks_plan(in_shape, kh: int, kw: int, c_out: int, n: int, stride: int = 1,
+                             pad: int = 0) -> dict | None:
+    """How conv2d_dense_blocks runs on the matrix cores, None on the routed kernel
+    (host only)."""
+    b, h, w, c_in = in_shape
+    info = (ctypes.c_int64 * 8)()
+    check("cs_conv2d_dense_blocks_plan", lib().cs_conv2d_dense_blocks_plan(
+        b, h, w, c_in, kh, kw, stride, pad, c_out, n, info))
+    if not info[0]:
+        return None
+    return {"rows": info[1], "groups": info[2], "segments": info[3], "tiles": info[4],
+            "workgroups": info[5], "slices": info[6], "steps": info[7]}
+
+
 def conv2d_dense(x: torch.Tensor, aug: torch.Tensor, kh: int, kw: int, n: int,
                  stride: int = 1, pad: int = 0, bias: torch.Tensor | None = None, pool: int = 1,
                  out: torch.Tensor | None = None) -> torch.Tensor:

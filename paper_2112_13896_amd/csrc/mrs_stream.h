@@ -254,12 +254,16 @@ struct TapPlace {
   uint32_t off;            // its list row's first entry, q * cap (modulo 2^32)
 };
 
-// The part of a pixel's list that a group of lanes takes (the whole list: 0, 0).
+// The part of a pixel's list that a group of lanes takes: all of it unless WIDE.
+template <bool WIDE>
 struct ListPart {
   int log2S;               // parts
   int s4;                  // 4 * this part
+  // place in the list of the part's chunk at pos (a multiple of four)
+  __device__ __forceinline__ int at(int pos) const { return WIDE ? (pos << log2S) + s4 : pos; }
   // entries of this part among the first m of the list
   __device__ __forceinline__ int count(int m) const {
+    if (!WIDE) return m;
     const int rounds = m >> (log2S + 2), rest = m - (rounds << (log2S + 2));
     return 4 * rounds + max(0, min(rest - s4, 4));
   }
@@ -273,20 +277,21 @@ struct StreamPre {
   BChunk ch[STREAM_PRE];
 };
 
+template <bool WIDE>
 __device__ __forceinline__ void stream_load(BChunk& c, const uint16_t* __restrict__ lidx,
                                             const float* __restrict__ lval, uint32_t base, int pos,
-                                            int cap, ListPart part) {
-  // pos a multiple of four; inside the row
-  const size_t e = (size_t)(base + (uint32_t)min((pos << part.log2S) + part.s4, cap - 4));
+                                            int cap, ListPart<WIDE> part) {
+  const size_t e = (size_t)(base + (uint32_t)min(part.at(pos), cap - 4));    // inside the row
   c.idx = *reinterpret_cast<const uint2*>(lidx + e);
   c.val = *reinterpret_cast<const float4*>(lval + e);
 }
 
+template <bool WIDE>
 __device__ __forceinline__ void stream_prefetch(StreamPre& tp, const uint16_t* __restrict__ lidx,
                                                 const float* __restrict__ lval,
                                                 const int32_t* __restrict__ lcnt,
                                                 const ConvGeom& geo, const TapPlace& pl, int t,
-                                                int j0, const FastDiv& fd_kw, ListPart part) {
+                                                int j0, const FastDiv& fd_kw, ListPart<WIDE> part) {
   const int ky = (int)fdiv((uint32_t)t, fd_kw), kx = t - ky * geo.KW;         // uniform
   const bool in = t < geo.KH * geo.KW;
   const uint32_t dq = in ? (uint32_t)(ky * geo.W + kx) : 0u;
@@ -344,12 +349,12 @@ __device__ __forceinline__ void stream_route(const float (&x)[4], const uint2 (&
 // are so done once per entry and quad, and the broadcasts fold into the
 // instruction that uses them (a DPP operand of the address add).  Returns the
 // list position where the quad stopped.
-template <int GB, bool CH>
+template <int GB, bool CH, bool WIDE>
 __device__ __forceinline__ int stream_tap(const StreamPre& tp, const uint16_t* __restrict__ lidx,
                                           const float* __restrict__ lval, int cap, int j0, int c_hi,
                                           int row_add, const unsigned char* smem, uint32_t tab,
                                           int log2row, uint32_t lane_tab,
-                                          const uint32_t (&col)[GB], ListPart part) {
+                                          const uint32_t (&col)[GB], ListPart<WIDE> part) {
   if (tp.off < 0) return j0;
   const int m = part.count(min(tp.cnt, cap));
   const uint32_t row0 = tab + ((uint32_t)row_add << log2row);
@@ -468,7 +473,7 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
   // part of its pixel's list a group of U lanes
   const int set0 = WIDE ? (int)blockIdx.y << sa.log2G : 0, ch0 = set0 << sa.log2n;
   const int log2S = WIDE ? sa.log2S : 0;
-  const ListPart part{log2S, WIDE ? 4 * ((tid >> sa.log2U) & ((1 << log2S) - 1)) : 0};
+  const ListPart<WIDE> part{log2S, WIDE ? 4 * ((tid >> sa.log2U) & ((1 << log2S) - 1)) : 0};
   float* acc = reinterpret_cast<float*>(smem);           // [KP][STREAM_BD]
   const int log2row = sa.log2G + 3;                      // bytes of a table row
   const uint32_t lane_tab = (uint32_t)(u * GB * 8);
@@ -551,7 +556,7 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
         StreamPre nxt;
         stream_prefetch(nxt, lidx, lval, lcnt, geo, place, t + 1, 0, sa.fd_kw, part);
         if (t == t0 && has_next) copy_block((blk + 1) * sa.RB, tnext);
-        stream_tap<GB, false>(q, lidx, lval, geo.cap, 0, C, (t - t0) * C, smem, toff, log2row,
+        stream_tap<GB, false, WIDE>(q, lidx, lval, geo.cap, 0, C, (t - t0) * C, smem, toff, log2row,
                               lane_tab, col, part);
         q = nxt;
       }
@@ -562,7 +567,7 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
       const int c_lo = (blk - t0 * sa.cblocks) * sa.RB;
       if (c_lo == 0) cursor = 0;
       if (has_next) copy_block((blk + 1) * sa.RB, tnext);
-      cursor = stream_tap<GB, true>(q, lidx, lval, geo.cap, cursor, c_lo + sa.RB, -c_lo, smem, toff,
+      cursor = stream_tap<GB, true, WIDE>(q, lidx, lval, geo.cap, cursor, c_lo + sa.RB, -c_lo, smem, toff,
                                     log2row, lane_tab, col, part);
       const int tn = (blk + 1) / sa.cblocks;
       stream_prefetch(q, lidx, lval, lcnt, geo, place, has_next ? tn : T_, tn == t0 ? cursor : 0,

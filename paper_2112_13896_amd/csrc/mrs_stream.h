@@ -23,9 +23,10 @@
 // blocks staged through registers into one buffer between two barriers; 1.5
 // workgroups of four wavefronts a compute unit): 14x14x256 3x3, 64 images, 26 of
 // 256 in and out 41.7 -> 36.2 us; 1x1 1024 -> 256, 102 in 33.0 -> 27.1 us; 56x56x128
-// 3x3/2, 13 images, 16 of 128 28.4 -> 20.8 us.  Of the 3x3 layer's time the vector
-// units are busy a little over half; reading a chunk's table entries a chunk
-// ahead, or four entries' accumulators together, changed nothing (36.0, 37.1 us).
+// 3x3/2, 13 images, 16 of 128 28.4 -> 20.8 us.  The 3x3 layer's 9.8 M vector
+// instructions are four cycles each on the 968 SIMDs it runs on, 47 % of its time;
+// reading a chunk's table entries a chunk ahead, or four entries' accumulators
+// together, changed nothing (36.0, 37.1 us).
 //
 // The sums alone of a 1x1 layer of more than 256 channels whose table fits a block in
 // slices of 256 channels take the same kernel (WIDE), a slice a workgroup (grid y).  The
@@ -70,7 +71,7 @@ struct StreamArgs {
   int write_sums;
   int log2Us;         // lanes per k-WTA unit
   uint32_t off_t0, off_t1;   // LDS byte offsets of the table buffers
-  int row_stride;     // WIDE: bytes of a table row in memory, all G sets
+  int row_stride;     // bytes of a table row in memory, all G sets
   int log2S;          // WIDE: parts of a pixel's list, at most 4; P = threads / (U S)
   int pairs;          // WIDE: the parts are added in pairs, not in order
   FastDiv fd_wo, fd_ho, fd_kw;
@@ -490,9 +491,7 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
     for (int p = wv; p * STREAM_PIECE < bytes; p += nwv) {           // uniform
       const int at = p * STREAM_PIECE + 16 * (tid & 63);
       const int row = min(at >> log2row, rows - 1);
-      const int64_t g = WIDE ? (int64_t)(r0 + row) * sa.row_stride + set0 * 8 +
-                                   (at & ((1 << log2row) - 1))
-                             : ((int64_t)(r0 + row) << log2row) + (at & ((1 << log2row) - 1));
+      const int64_t g = (int64_t)(r0 + row) * sa.row_stride + set0 * 8 + (at & ((1 << log2row) - 1));
       __builtin_amdgcn_global_load_lds(
           reinterpret_cast<const __attribute__((address_space(1))) void*>(
               reinterpret_cast<uintptr_t>(aug) + (uintptr_t)g),
@@ -556,8 +555,8 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
         StreamPre nxt;
         stream_prefetch(nxt, lidx, lval, lcnt, geo, place, t + 1, 0, sa.fd_kw, part);
         if (t == t0 && has_next) copy_block((blk + 1) * sa.RB, tnext);
-        stream_tap<GB, false, WIDE>(q, lidx, lval, geo.cap, 0, C, (t - t0) * C, smem, toff, log2row,
-                              lane_tab, col, part);
+        stream_tap<GB, false, WIDE>(q, lidx, lval, geo.cap, 0, C, (t - t0) * C, smem, toff,
+                                    log2row, lane_tab, col, part);
         q = nxt;
       }
     } else {
@@ -567,8 +566,8 @@ __global__ __launch_bounds__(STREAM_BD, 4) void mrs_stream_f32(
       const int c_lo = (blk - t0 * sa.cblocks) * sa.RB;
       if (c_lo == 0) cursor = 0;
       if (has_next) copy_block((blk + 1) * sa.RB, tnext);
-      cursor = stream_tap<GB, true, WIDE>(q, lidx, lval, geo.cap, cursor, c_lo + sa.RB, -c_lo, smem, toff,
-                                    log2row, lane_tab, col, part);
+      cursor = stream_tap<GB, true, WIDE>(q, lidx, lval, geo.cap, cursor, c_lo + sa.RB, -c_lo, smem,
+                                          toff, log2row, lane_tab, col, part);
       const int tn = (blk + 1) / sa.cblocks;
       stream_prefetch(q, lidx, lval, lcnt, geo, place, has_next ? tn : T_, tn == t0 ? cursor : 0,
                       sa.fd_kw, part);

@@ -428,8 +428,9 @@ def ab_stem(batch: int = 32) -> dict:
     """A ResNet-50 stem with block Complementary Sparsity (Section 5: a pixel's
     RGB values one block; 7x7, stride 2, pad 3, 64 outputs, n = 4: 75 % of
     the weights zero) on a dense int8 224x224x3 batch: the sparse-dense block
-    kernel (cs_conv2d_dense_blocks, one dot product and one routed add per
-    tap and set) against the routed path on the compacted input (cs_conv2d).
+    layer (cs_conv2d_dense_blocks, on the matrix cores, each block's Kernel ID
+    routing its weights once) against the routed path on the compacted input
+    (cs_conv2d).
     Synthetic seeded data; warm timings (20-launch graphs); the two sums must
     be equal."""
     import torch

@@ -191,9 +191,9 @@ int cs_mrs_kwta_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval, const
  * k winners (Section 5: channels partitioned into independent modules, each
  * with its own k-WTA; the ResNet-50 stages use units of 64 channels).  fp32
  * only (unit == c_out: exactly cs_mrs_kwta_conv2d, any dtype, ot = the sums'
- * dtype).  DEVICE memory.  One kernel when the layer runs on the table-block
- * kernel with the selection on the lanes' own accumulators (no pooling,
- * power-of-two sets and kernels per set, n <= 16, c_out <= 256, a unit a
+ * dtype).  DEVICE memory.  One kernel when the layer runs on the table-block or
+ * the streamed-table kernel with the selection on the lanes' own accumulators (no
+ * pooling, power-of-two sets and kernels per set, n <= 16, c_out <= 256, a unit a
  * power-of-two number of a pixel's lanes); otherwise cs_mrs_conv2d and
  * cs_kwta on the [rows * c_out / unit][unit] view of y, dense output only.
  *
@@ -224,8 +224,9 @@ int cs_mrs_kwta_units_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval,
  *          kernel, 2 fused layer kernel, 3 one workgroup per sample: a layer
  *          whose window is the whole unpadded input map, output 1 x 1, no
  *          pool - a linear layer; 4 input-stationary int8 convolution; 5 one
- *          wavefront per item: a 1x1 layer with many items and a k-WTA over
- *          rows of more than 128 or k > 32; 6 fp32 layer without pooling,
+ *          wavefront per item: an int8 1x1 layer of at least 128 items, the
+ *          sums alone or with a k-WTA over rows of more than 128 channels or
+ *          k > 32; 6 fp32 layer without pooling,
  *          sets and kernels per set powers of two, n <= 16, c_out <= 256:
  *          tiles complete in the channel dimension with the packed table
  *          streamed through LDS in blocks of rows, k-WTA in the epilogue; and
@@ -238,9 +239,11 @@ int cs_mrs_kwta_units_conv2d(cs_dtype xt, const uint16_t* idx, const void* lval,
  *          the table, whose lanes select as in 5), [2] table rows per
  *          block, [3] blocks, with [1] = 9 [4] channel slices and [5] log2 of
  *          the parts a pixel's list is added in (of the slices), [6]
- *          workgroups, [7] LDS bytes, [8] sets per lane; for paths 3 and
- *          5: [6] workgroups, [7] LDS bytes per workgroup, [8] entry slices
- *          per packed set; for path 4: [2] output rows per band, [6]
+ *          workgroups, [7] LDS bytes, [8] sets per lane; for path 3:
+ *          [6] workgroups, [7] LDS bytes per workgroup, [8] entry slices per
+ *          packed set; for path 5: [6] and [7] as for 3 (an estimate: the launch
+ *          asks the device), [8] channels a lane holds at most, one of every 64;
+ *          for path 4: [2] output rows per band, [6]
  *          workgroups, [7] LDS bytes, [8] sets per lane; for path 2: [1] tile mode (0 rows of
  *          items, 1 image rectangles), [2] items (mode 0) or pooled rows
  *          (mode 1) per tile, [3] pooled columns per tile (mode 1), [4] list

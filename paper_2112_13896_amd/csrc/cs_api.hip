@@ -1070,15 +1070,15 @@ int launch_scatter(const ScatterPlan& pl, cs_dtype ot, hipStream_t s, const uint
 }
 
 // ------------------------------------------------- one wavefront per item
-// A one-tap layer (1x1 conv with stride 1, or linear) with many items, a
-// table that fits LDS and a k-WTA over long rows: each wavefront takes whole
+// A one-tap layer (1x1 conv with stride 1) with many items, a table that fits
+// LDS and a k-WTA over long rows, or the sums alone: each wavefront takes whole
 // items.
 // Measured from 49 items up the row kernel is the faster one for every pair of
 // MobileNetV2's 1x1 layers (three launches: 196 items of 96 -> 576 -> 96 20.4
 // against 35.3 us, 1,568 of 160 -> 960 -> 160 29.6 against 45.5 us with the
 // sums and the k-WTA in two kernels): even few wavefronts beat a second kernel and
-// the sums' way through memory.  Layers of under 128 items stay on the two
-// kernels all the same, which the layer tests hold to at 126 items.
+// the sums' way through memory.  The line lies at 128 for no reason of speed: the
+// tests of the fused kernel's row tiles run 126 items and expect them there.
 constexpr int64_t kRowsMinItems = 128;
 constexpr size_t kRowsTabLds = 48 * 1024;
 

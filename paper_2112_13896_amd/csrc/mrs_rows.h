@@ -1,7 +1,7 @@
 // One wavefront per item: Multiply, Route and Sum (Section 3.2 steps 3-5)
 // and k-WTA (Section 3.3.3) for an int8 layer whose window is one tap (a 1x1
-// convolution with stride 1, or a linear layer) with many items, each with a
-// short list and a row of 129-2048 outputs or a k over 32.
+// convolution with stride 1) with many items, each with a short list and a row of
+// 129-2048 outputs or a k over 32, or the sums alone.
 //
 //  * the workgroup stages the packed table (value and Kernel ID per slot, the
 //    ID already turned into the byte offset of its accumulator within the
@@ -29,9 +29,9 @@
 //    with consecutive lanes on consecutive entries, then the row is put back to
 //    the bias for the next item.
 //
-// What bounds it: the issue of a wavefront's serial chain (about 1,000
-// instructions an item, 440 of them vector, six to eight wavefronts a SIMD) and,
-// behind it, the LDS adds.  25,088 items, 96 -> 576 in sets of eight, 12 entries,
+// What bounds it: the issue of a wavefront's serial chain (990 instructions an
+// item, 480 of them vector, its share of the wavefront's set-up included; six to
+// eight wavefronts a SIMD) and, behind it, the LDS adds.  25,088 items, 96 -> 576 in sets of eight, 12 entries,
 // 72 winners as int8 lists: 46.1 -> 32.5 us (740 vector instructions an item
 // before: a full histogram pass per nine bits, list positions by scans over
 // strided lanes, an item loop compiled as divergent); the 576 -> 96 sums of the

@@ -6,8 +6,9 @@
 // LDS); each workgroup reads only the rows its sample's non-zeros select.
 //
 //  * the sample's (index, value) lists (or its dense row, the zeros left out)
-//    are staged in LDS as one flat entry list (pixel order, then list order); entry (pixel p, index c) uses table
-//    row p*C + c, the window's taps being the map's pixels;
+//    are staged in LDS as one flat entry list (pixel order, then list order);
+//    entry (pixel p, index c) uses table row p*C + c, the window's taps being the
+//    map's pixels;
 //  * a job (slice s, set g) runs over one contiguous range of entries: it
 //    reads aug[row][g] straight from global memory (the lanes of a wavefront
 //    read one contiguous row segment; the table stays in L2), SAMPLE_BATCH

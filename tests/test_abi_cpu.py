@@ -702,3 +702,18 @@ def test_fast_division_formula():
         for n in ns:
             if 0 <= n < 2 ** 32:
                 assert (((n * m) >> 32) + n) >> s == n // d
+
+
+def test_dense_blocks_plan_arguments(L):
+    """cs_conv2d_dense_blocks_plan refuses what the call refuses and reports the
+    routed kernel where the matrix cores do not take the layer."""
+    info = (ctypes.c_int64 * 8)()
+    plan = L.cs_conv2d_dense_blocks_plan
+    assert plan(1, 8, 8, 3, 3, 3, 1, 1, 64, 4, None) == CS_ERR_ARG
+    assert plan(0, 8, 8, 3, 3, 3, 1, 1, 64, 4, info) == CS_ERR_ARG
+    assert plan(1, 8, 8, 5, 3, 3, 1, 1, 64, 4, info) == CS_ERR_SHAPE
+    assert plan(1, 8, 8, 3, 3, 3, 1, 1, 64, 33, info) == CS_ERR_SHAPE
+    assert ops.conv2d_dense_blocks_plan((1, 8, 8, 3), 3, 3, 64, 4, 1, 1)["steps"] == 1
+    assert ops.conv2d_dense_blocks_plan((1, 8, 8, 3), 3, 3, 24, 4, 1, 1) is None     # channels
+    assert ops.conv2d_dense_blocks_plan((1, 24, 24, 3), 9, 9, 64, 4, 1, 4) is None   # window
+    assert ops.conv2d_dense_blocks_plan((1, 1, 1, 3), 1, 1, 64, 4, 1, 0) is None     # image

@@ -260,8 +260,9 @@ int cs_mrs_plan(cs_dtype xt, int cap, int b, int h, int w, int c_in, int kh, int
  * cs_linear - a whole sparse-sparse linear layer: cs_compact of x into the
  * workspace, then Multiply/Route/Sum (a linear layer is the 1x1 convolution
  * of 1x1 images); in one launch, the workspace untouched, when the layer runs
- * with a workgroup per sample, there are at most 1,024 samples or their rows
- * have at least 2,048 elements, and y shares no memory with x.  DEVICE memory.
+ * with a workgroup per sample, there are at most 1,024 samples (fp32: 2,048) or
+ * their rows have at least 2,048 elements, and y shares no memory with x.  DEVICE
+ * memory.
  *
  *  x       device [batch][d_in] (int8 or fp32), d_in <= CS_MAX_ROW.
  *  aug     device augmented packed tensor [d_in][G] from cs_pack of [d_out][d_in].

@@ -1520,11 +1520,13 @@ WsLayout ws_layout(cs_dtype xt, int64_t rows, int c_in) {
 // The dense-input kernel ranks a sample's non-zeros with one workgroup's barriers, which
 // few samples hide behind the launch it saves, and many short ones do not: 8,192 rows of
 // 64 -> 32 int8 86.5 us against 72.4 us for compaction and the list kernel (2,048 rows
-// 23.4 and 21.9; 1,024 rows 12.5 and 13.4), 512 -> 512 fp32 with k-WTA 213.5 and 206.1
-// (28.7 and 30.4).  Rows of 2,048 elements stay ahead or level at any batch (8,192 rows,
-// 2,048 -> 1,000: int8 164.5 and 167.0, fp32 215.4 and 223.6).
-bool dense_sample_pays(const cs::ConvGeom& geo) {
-  return geo.B <= 4 * kPlanCus || (int64_t)geo.H * geo.W * geo.C >= 2048;
+// 23.4 and 21.9; 1,024 rows 12.5 and 13.4).  fp32, whose rows are longer to compact, lies
+// a factor of two higher: 512 -> 512 sums 8,192 rows 98.9 and 95.6, 2,048 rows 26.5 and
+// 27.7, with k-WTA 213.5 and 206.1, 55.0 and 55.1.  Rows of 2,048 elements stay ahead or
+// level at any batch (8,192 rows, 2,048 -> 1,000: int8 164.5 and 167.0, fp32 215.4 and
+// 223.6).
+bool dense_sample_pays(const cs::ConvGeom& geo, cs_dtype xt) {
+  return geo.B <= (xt == CS_F32 ? 8 : 4) * kPlanCus || (int64_t)geo.H * geo.W * geo.C >= 2048;
 }
 
 // Whether n bytes at p and the dense input x share memory.  In one launch a sample's
@@ -1542,7 +1544,7 @@ bool shares_input(const void* x, cs_dtype xt, const cs::ConvGeom& geo, const voi
 int dense_launch(cs_dtype xt, const void* x, const cs::ConvGeom& geo, const void* aug,
                  const void* bias, void* y, uint16_t* idx, void* lv, int32_t* cnt, hipStream_t s) {
   SamplePlan sp;
-  if (dense_sample_pays(geo) && sample_plan(geo, xt, -1, 0, 1, &sp) &&
+  if (dense_sample_pays(geo, xt) && sample_plan(geo, xt, -1, 0, 1, &sp) &&
       !shares_input(x, xt, geo, y, (size_t)geo.B * geo.c_out * 4)) {
     const cs::ListOut none{nullptr, nullptr, nullptr, 0};
     if (xt == CS_F32)
@@ -2256,7 +2258,7 @@ int cs_conv2d_kwta(cs_dtype xt, const void* x, int b, int h, int w, int c_in, in
                       (lists && (shares_input(x, xt, geo, oidx, (size_t)b * ocap * 2) ||
                                  shares_input(x, xt, geo, oval, (size_t)b * ocap * ob) ||
                                  shares_input(x, xt, geo, ocnt, (size_t)b * 4)));
-  if (h == 1 && w == 1 && !shared && dense_sample_pays(geo) &&
+  if (h == 1 && w == 1 && !shared && dense_sample_pays(geo, xt) &&
       sample_plan(geo, xt, k, shift, keep_sums, &sp)) {
     const cs::ListOut lo{oidx, oval, ocnt, lists ? ocap : 0};
     if (xt == CS_F32)

@@ -92,12 +92,13 @@ def test_dense_input_equals_lists(case, offset):
             assert torch.equal(got[1][i, :c], want[1][i, :c])
 
 
-@pytest.mark.parametrize("dt", ["i8", "f32"])
-@pytest.mark.parametrize("b, d_in, one", [(1024, 64, True), (1025, 64, False), (1100, 2044, False),
-                                          (1100, 2048, True)])
+@pytest.mark.parametrize("dt, b, d_in, one", [
+    ("i8", 1024, 64, True), ("i8", 1025, 64, False), ("i8", 1100, 2044, False),
+    ("i8", 1100, 2048, True), ("f32", 2048, 64, True), ("f32", 2049, 64, False),
+    ("f32", 2100, 2044, False), ("f32", 2100, 2048, True)])
 def test_one_launch_only_where_it_pays(dt, b, d_in, one):
-    """Up to 1,024 samples, or rows of 2,048 elements, take one launch and leave
-    the list buffers alone; more and shorter rows are compacted first.  The
+    """Up to 1,024 samples (fp32 2,048), or rows of 2,048 elements, take one launch
+    and leave the list buffers alone; more and shorter rows are compacted first.  The
     results are the lists' either way."""
     r = np.random.default_rng(b + d_in)
     n, d_out, k = 4, 32, 6
